@@ -235,8 +235,12 @@ struct Engine {
        *spin_n = nullptr, *spin_hat = nullptr, *eta = nullptr;
     d4 *sc_x = nullptr, *sc_f = nullptr, *sc_g = nullptr, *sc_dF = nullptr, *sc_dG = nullptr;
     double *sc_part = nullptr, *sc_out = nullptr;
-    int *nbrR = nullptr, *cntR = nullptr, *cntFeR = nullptr, *revR = nullptr;
-    int *nbrA = nullptr, *cntA = nullptr, *cntFeA = nullptr, *revA = nullptr, *a2r = nullptr;
+    int *rowR = nullptr, *lenR = nullptr, *lenFeR = nullptr;
+    int *actR = nullptr, *cntR = nullptr, *cntFeR = nullptr;
+    int *actA = nullptr, *cntA = nullptr, *cntFeA = nullptr;
+    uint8_t *r2a = nullptr, *revA = nullptr;
+    uint16_t *actS = nullptr, *xS = nullptr;
+    float4 *pos4 = nullptr;
     int *cell_of = nullptr, *cell_cnt = nullptr, *cell_start = nullptr, *cell_fill = nullptr, *cell_atoms = nullptr;
     int *flags = nullptr;
     int *act_buf = nullptr;    // [2 cap_rep] 'active' words to set on a re-layout (-1: leave)
@@ -310,8 +314,8 @@ struct Engine {
         put(pos); put(vel); put(spin); put(force); put(field); put(pos_ref);
         put(spin_n); put(spin_hat); put(eta);
         put(sc_x); put(sc_f); put(sc_g); put(sc_dF); put(sc_dG); put(sc_part); put(sc_out);
-        put(nbrR); put(cntR); put(cntFeR); put(revR);
-        put(nbrA); put(cntA); put(cntFeA); put(revA); put(a2r);
+        put(rowR); put(lenR); put(lenFeR); put(r2a); put(revA);
+        put(actR); put(cntR); put(cntFeR); put(actA); put(cntA); put(cntFeA); put(actS); put(xS); put(pos4);
         put(cell_of); put(cell_cnt); put(cell_start); put(cell_fill); put(cell_atoms);
         put(flags); put(chunks); put(chunk_ptr); put(col_idx); put(colpos); put(col_rid); put(cpl_j); put(cpl_n);
         put(partial); put(obs); put(act_buf);
@@ -349,8 +353,9 @@ struct Engine {
         S.col_idx = col_idx;
         S.colpos = colpos;
         S.col_rid = col_rid;
-        S.nbrR = nbrR; S.cntR = cntR; S.cntFeR = cntFeR; S.revR = revR;
-        S.nbrA = nbrA; S.cntA = cntA; S.cntFeA = cntFeA; S.revA = revA; S.a2r = a2r;
+        S.rowR = rowR; S.lenR = lenR; S.lenFeR = lenFeR; S.r2a = r2a; S.revA = revA;
+        S.actR = actR; S.cntR = cntR; S.cntFeR = cntFeR;
+        S.actA = actA; S.cntA = cntA; S.cntFeA = cntFeA; S.actS = actS; S.xS = xS; S.pos4 = pos4;
         S.cell_of = cell_of; S.cell_cnt = cell_cnt; S.cell_start = cell_start; S.cell_fill = cell_fill;
         S.cell_atoms = cell_atoms;
         S.flags = flags;
@@ -409,8 +414,8 @@ struct Engine {
             put(pos); put(vel); put(spin); put(force); put(field); put(pos_ref);
             put(spin_n); put(spin_hat); put(eta);
             put(sc_x); put(sc_f); put(sc_g); put(sc_dF); put(sc_dG); put(sc_part);
-            put(nbrR); put(cntR); put(cntFeR); put(revR);
-            put(nbrA); put(cntA); put(cntFeA); put(revA); put(a2r);
+            put(rowR); put(lenR); put(lenFeR); put(r2a); put(revA);
+            put(actR); put(cntR); put(cntFeR); put(actA); put(cntA); put(cntFeA); put(actS); put(xS); put(pos4);
             put(cell_of); put(cell_atoms); put(cpl_j); put(cpl_n);
             if (work && !arena) (void)hipFree(work);
             work = nullptr;
@@ -419,10 +424,12 @@ struct Engine {
                 (rc = get(&pos, c)) || (rc = get(&vel, c)) || (rc = get(&spin, c)) ||
                 (rc = get(&force, c)) || (rc = get(&field, c)) || (rc = get(&pos_ref, c)) ||
                 (rc = get(&spin_n, c)) || (rc = get(&spin_hat, c)) || (rc = get(&eta, c)) ||
-                (rc = get(&nbrR, (size_t)MAXR * c)) || (rc = get(&cntR, c)) || (rc = get(&cntFeR, c)) ||
-                (rc = get(&revR, (size_t)MAXR * c)) || (rc = get(&nbrA, (size_t)MAXA * c)) ||
-                (rc = get(&cntA, c)) || (rc = get(&cntFeA, c)) || (rc = get(&revA, (size_t)MAXA * c)) ||
-                (rc = get(&a2r, (size_t)MAXA * c)) || (rc = get(&cell_of, c)) ||
+                (rc = get(&rowR, (size_t)MAXR * c)) || (rc = get(&lenR, c)) || (rc = get(&lenFeR, c)) ||
+                (rc = get(&actR, (size_t)MAXR * c)) || (rc = get(&cntR, c)) || (rc = get(&cntFeR, c)) ||
+                (rc = get(&xS, (size_t)MAXFE * cf)) || (rc = get(&pos4, c)) ||
+                (rc = get(&r2a, (size_t)MAXR * c)) || (rc = get(&revA, (size_t)MAXA * c)) ||
+                (rc = get(&actA, (size_t)MAXA * c)) || (rc = get(&actS, (size_t)MAXA * c)) ||
+                (rc = get(&cntA, c)) || (rc = get(&cntFeA, c)) || (rc = get(&cell_of, c)) ||
                 (rc = get(&cell_atoms, c)) || (rc = get(&cpl_j, (size_t)MAXFE * cf)) ||
                 (rc = get(&cpl_n, cf)) || (rc = get(&sc_x, cf)))
                 return rc;
@@ -747,6 +754,7 @@ struct Engine {
         HIPCHK(hipStreamSynchronize(st));
         if (N) {
             const Sys S = sys();
+            launch_pos4(S, st);
             launch_rebuild(S, RC_R + max_skin(), RC_A + max_skin(), st);
             // Replicas carried over from the previous layout keep their forces
             // and fields: neighbour order inside a replica does not depend on
@@ -801,7 +809,16 @@ struct Engine {
         { ProfScope p(this, 5); launch_gather(S, w, st); }
     }
 
+    // the in-cutoff lists after the positions (or the Verlet lists) changed
+    void activate(int mode) {
+        ProfScope p(this, 8);
+        if (prec == SL_FP64) launch_active<double>(sys(), mode, st);
+        else launch_active<float>(sys(), mode, st);
+    }
+
+    // forces, fields and energies at the present positions and spins
     void evaluate(const d4 *spins) {
+        activate(PASS_FULL);
         if (prec == SL_FP64) {
             forward(M->m64, w64, spins);
             backward(M->m64, w64);
@@ -880,6 +897,7 @@ struct Engine {
         rebuild_if_needed();
         { ProfScope p(this, 9); launch_langevin(S, st); }
         if (!M->structural) {
+            activate(PASS_SPIN);
             if (prec == SL_FP64) spin_step(M->m64, w64);
             else spin_step(M->m32, w32);
         }

@@ -9,6 +9,9 @@ constexpr int MAXFE = 64;     // listed spin-carrying neighbours kept for the sp
 constexpr int RCOEF = 4 * NB; // per-atom contracted radial-set coefficients
 constexpr int MCOEF = 3 * NB; // per-spin-carrier contracted magnetic pair coefficients
 
+constexpr int NO_SLOT = 255;  // r2a of a listed neighbour beyond rc_A + skin
+constexpr int ANG_BIT = (int)0x80000000;   // on a row's entries within rc_A + skin
+
 // flags[] words
 enum { F_REBUILD = 0, F_OVERFLOW = 1, F_COLOUR = 2, F_NONFINITE = 3, NFLAGS = 8 };
 
@@ -30,8 +33,22 @@ struct Sys {
     const int *col_idx;    // [N_fe] spin carriers grouped by colour
     const int *colpos;     // [N_fe] position of each spin carrier in col_idx
     const int *col_rid;    // [N_fe] replica of each entry of col_idx
-    int *nbrR, *cntR, *cntFeR, *revR;
-    int *nbrA, *cntA, *cntFeA, *revA, *a2r;
+    // Verlet rows (slot-major [slot][N]) within rc_R + skin, spin carriers first,
+    // ANG_BIT set on entries within rc_A + skin, which are numbered in row order
+    // (angular slots); r2a: the angular slot of a row's entry, NO_SLOT on the
+    // others; revA: the angular slot of i in the row of the neighbour at angular
+    // slot a
+    int *rowR, *lenR, *lenFeR;
+    uint8_t *r2a, *revA;
+    // neighbours inside the cutoffs at the present positions, in row order, with
+    // their counts: inside rc_R rank-major [rank][N] (for a lane per atom);
+    // inside rc_A atom-major [N][MAXA] (for the lanes of eight atoms together)
+    // with own | reverse angular slot << 8 of each (actS), the latter also
+    // [rank][N_fe] at the rc_R rank of spin pairs (xS)
+    int *actR, *cntR, *cntFeR;
+    int *actA, *cntA, *cntFeA;
+    uint16_t *actS, *xS;
+    float4 *pos4;          // positions in single precision, for the cutoff tests that are not close
     int *cell_of, *cell_cnt, *cell_start, *cell_fill, *cell_atoms;
     int *flags;
 };
@@ -60,7 +77,7 @@ struct Work {
     real *pbA;                  // angular pair records [MAXA][N][4]: dE_i/dd_ij, h_ij, stored likewise
     real *ownR;                 // [N][6]: radial and single-ion sum_j dE_i/dd_ij, dE_i/ds_i
     real *ownA;                 // [N][6]: angular-set sum_j dE_i/dd_ij, sum_j h_ij s_j
-    real *csa;                  // [MAXFE][N_fe]: spin-angular part of a_ij at j's slot in i's rc_R row (atom order)
+    real *csa;                  // [MAXFE][N_fe]: spin-angular part of a_ij at j's angular slot (atom order)
     real *cpl;                  // [MAXFE][N_fe][6]: J, D, K, rhat (colour-list order)
     real *selfc;                // [N_fe][8]: A_i (xx yy zz xy xz yz), o_i (colour-list order)
     int *cpl_j;                 // [MAXFE][N_fe]: neighbour of each coupling (colour-list order)
@@ -75,6 +92,10 @@ void launch_rebuild(const Sys &S, double r_listR, double r_listA, hipStream_t st
 // mid positions, and its later passes at the same positions
 enum { PASS_FULL = 0, PASS_SPIN = 1, PASS_SPIN_REUSE = 2 };
 
+// the lists of neighbours inside the cutoffs at the present positions, of every
+// atom or (the spin step) of the spin carriers
+template <typename real>
+void launch_active(const Sys &S, int mode, hipStream_t st);
 template <typename real>
 void launch_desc_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &W, const d4 *spin, int mode,
                         hipStream_t st);
@@ -98,7 +119,8 @@ template <typename real>
 void launch_sweep(const Sys &S, const Work<real> &W, const int *col_ptr_host, int n_colours, hipStream_t st);
 
 void launch_kick(const Sys &S, hipStream_t st);
-void launch_drift(const Sys &S, hipStream_t st);
+void launch_drift(const Sys &S, hipStream_t st);   // also refreshes pos4
+void launch_pos4(const Sys &S, hipStream_t st);    // pos4 from pos
 void launch_langevin(const Sys &S, hipStream_t st);
 void launch_spin_prep(const Sys &S, hipStream_t st);
 void launch_spin_restore(const Sys &S, hipStream_t st);

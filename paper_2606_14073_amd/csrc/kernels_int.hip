@@ -39,6 +39,14 @@ __global__ void k_drift(Sys S) {
     if (R.pbc[1]) p.y -= R.box[1] * floor(p.y / R.box[1]);
     if (R.pbc[2]) p.z -= R.box[2] * floor(p.z / R.box[2]);
     S.pos[i] = p;
+    S.pos4[i] = make_float4((float)p.x, (float)p.y, (float)p.z, 0.0f);
+}
+
+__global__ void k_pos4(Sys S) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= S.N) return;
+    const d4 p = S.pos[i];
+    S.pos4[i] = make_float4((float)p.x, (float)p.y, (float)p.z, 0.0f);
 }
 
 __device__ inline double temperature(const RepDev &R) { return R.T0 + (R.T1 - R.T0) * ramp_frac(R); }
@@ -730,6 +738,9 @@ void launch_kick(const Sys &S, hipStream_t st) {
 }
 void launch_drift(const Sys &S, hipStream_t st) {
     if (S.N) hipLaunchKernelGGL(k_drift, dim3(nblk(S.N, 256)), dim3(256), 0, st, S);
+}
+void launch_pos4(const Sys &S, hipStream_t st) {
+    if (S.N) hipLaunchKernelGGL(k_pos4, dim3(nblk(S.N, 256)), dim3(256), 0, st, S);
 }
 void launch_langevin(const Sys &S, hipStream_t st) {
     if (S.N) hipLaunchKernelGGL(k_langevin, dim3(nblk(S.N, 256)), dim3(256), 0, st, S);

@@ -106,6 +106,147 @@ __device__ inline real xor_sum8(real v) {
 }
 
 // -------------------------------------------------------------------------
+// Neighbours inside the cutoffs at the present positions, compacted in row
+// order: the Verlet rows hold a third more (the skin), at places that differ
+// from atom to atom, so every pair kernel that walked them spent that share of
+// its lanes on nothing. One pass per set of positions, eight lanes per atom
+// (ranks by ballot); the lists depend on the positions alone and not on which
+// farther atoms the rows happen to hold.
+// What bounds it is the gather of the neighbours' positions, one L1 access per
+// 16 bytes and lane: the test runs on the single-precision positions (one
+// access), and the few pairs that lie within its rounding error of a cutoff
+// are tested as the pair kernels compute r^2.
+// 2,097,152 atoms, FP64: 2.3 ms of a step for its two passes, against 6.8 ms
+// that the pair kernels no longer spend on the skin.
+// -------------------------------------------------------------------------
+
+// the cutoff tests of one atom; close() says that a test in single precision
+// does not decide
+template <typename real>
+struct CutTest {
+    static constexpr real rc = (real)RC_R, rca = (real)RC_A;
+    float px, py, pz, bx, by, bz, ix, iy, iz, tol;
+    __device__ void set(const Img &R, const d4 &pi) {
+        px = (float)pi.x, py = (float)pi.y, pz = (float)pi.z;
+        bx = (float)R.b[0], by = (float)R.b[1], bz = (float)R.b[2];
+        ix = (float)R.ib[0], iy = (float)R.ib[1], iz = (float)R.ib[2];
+        // Rounding of r^2 near a cutoff: coordinates, box edge and differences
+        // are at most M, each rounded by 2^-24 M or less, five of them per
+        // component; r below 7 A, so 2 sqrt(3) r e + 3 e^2 for the components
+        // and 1e-5 for the sum.
+        float M = fmaxf(fmaxf(fabsf(px), fabsf(py)), fabsf(pz));
+        M = fmaxf(M, fmaxf(fmaxf(bx, by), bz)) + 7.0f;
+        const float e = M * 3.0e-7f;
+        tol = 25.0f * e + 3.0f * e * e + 1.0e-5f;
+    }
+    __device__ float r2(const float4 &q) const {
+        float dx = q.x - px, dy = q.y - py, dz = q.z - pz;
+        dx -= bx * rintf(dx * ix);
+        dy -= by * rintf(dy * iy);
+        dz -= bz * rintf(dz * iz);
+        return dx * dx + dy * dy + dz * dz;
+    }
+    // inside rc_R, inside rc_A
+    __device__ void operator()(const Sys &S, const Img &R, int i, int j, const float4 &q, bool &in, bool &inA) const {
+        const float c2 = (float)(RC_R * RC_R), ca2 = (float)(RC_A * RC_A);
+        const float f2 = r2(q);
+        in = f2 < c2;
+        inA = f2 < ca2;
+        if (fabsf(f2 - c2) < tol || fabsf(f2 - ca2) < tol) {
+            real d[3];
+            const real x2 = geom_p(R, S.pos[i], S.pos[j], d);
+            in = x2 < rc * rc;
+            inA = x2 < rca * rca;
+        }
+    }
+};
+
+// The lists are put together in LDS and written in whole lines: stored by each
+// lane as it went along (its ranks differ from its neighbours') they left L2 in
+// parts, 3.8 times their bytes.
+template <typename real>
+__global__ void __launch_bounds__(256) k_active(Sys S, int n) {
+    constexpr int ATOMS = 32;
+    __shared__ int sR[MAXR * ATOMS];                        // [rank][atom]
+    __shared__ __align__(16) int sA[ATOMS * MAXA];          // [atom][rank]
+    __shared__ __align__(8) uint16_t sS[ATOMS * MAXA];
+    __shared__ uint16_t sX[MAXFE * ATOMS];                  // [rank][atom]
+    __shared__ int sn[2 * ATOMS];                           // entries of sR and sX
+    const int lane = threadIdx.x & 7, gbase = threadIdx.x & 56, at = threadIdx.x >> 3;
+    const int first = blockIdx.x * ATOMS;
+    const int i = live(S, first + at < n ? first + at : -1);
+    const size_t ld = S.N, lf = S.N_fe;
+    int nR = 0, nA = 0, nX = 0;
+    if (i >= 0) {
+        const Img R = img_of(S.rep[S.rid[i]]);
+        CutTest<real> cut;
+        cut.set(R, S.pos[i]);
+        const int len = S.lenR[i], lenfe = S.lenFeR[i];
+        const int mx = S.mag && i < S.N_fe ? MAXFE : 0;
+        const unsigned below = (1u << lane) - 1u;
+        int nL = 0, nFeR = 0, nFeA = 0;
+        // the row entry two rounds ahead, its position one round ahead
+        int vn = lane < len ? S.rowR[(size_t)lane * ld + i] : i;
+        int vm = lane + 8 < len ? S.rowR[(size_t)(lane + 8) * ld + i] : i;
+        float4 qn = S.pos4[vn & ~ANG_BIT];
+        for (int s0 = 0; s0 < len; s0 += 8) {
+            const int s = s0 + lane, v = vn, j = v & ~ANG_BIT;
+            const float4 q = qn;
+            vn = vm;
+            qn = S.pos4[vn & ~ANG_BIT];
+            vm = s + 16 < len ? S.rowR[(size_t)(s + 16) * ld + i] : i;
+            const bool listed = s < len, ang = listed && (v & ANG_BIT);
+            bool in = false, inA = false;
+            if (listed) cut(S, R, i, j, q, in, inA);
+            inA = inA && ang;
+            const unsigned mL = (unsigned)(__ballot(ang) >> gbase) & 0xffu;   // an entry's angular slot: the flagged ones before it
+            const unsigned mR = (unsigned)(__ballot(in) >> gbase) & 0xffu;
+            const unsigned mA = (unsigned)(__ballot(inA) >> gbase) & 0xffu;
+            const int kR = nR + __popc(mR & below);
+            int sr = 0;
+            if (inA) {
+                const int a = nL + __popc(mL & below), o = at * MAXA + nA + __popc(mA & below);
+                sr = a | (int)S.revA[(size_t)a * ld + i] << 8;
+                sA[o] = j;
+                sS[o] = (uint16_t)sr;
+            }
+            if (in) {
+                sR[kR * ATOMS + at] = j;
+                if (s < lenfe && kR < mx) sX[kR * ATOMS + at] = (uint16_t)sr;
+            }
+            nL += __popc(mL);
+            nR += __popc(mR);
+            nA += __popc(mA);
+            if (s0 < lenfe) {
+                const unsigned mf = lenfe - s0 < 8 ? (1u << (lenfe - s0)) - 1u : 0xffu;
+                nFeR += __popc(mR & mf);
+                nFeA += __popc(mA & mf);
+            }
+        }
+        nX = min(nFeR, mx);
+        if (lane == 0) {
+            S.cntR[i] = nR;
+            S.cntFeR[i] = nFeR;
+            S.cntA[i] = nA;
+            S.cntFeA[i] = nFeA;
+        }
+    }
+    if (lane == 0) {
+        sn[at] = nR;
+        sn[ATOMS + at] = nX;
+    }
+    __syncthreads();
+    const int a2 = threadIdx.x & (ATOMS - 1), r0 = threadIdx.x / ATOMS;
+    for (int r = r0; r < sn[a2]; r += 256 / ATOMS) S.actR[(size_t)r * ld + first + a2] = sR[r * ATOMS + a2];
+    for (int r = r0; r < sn[ATOMS + a2]; r += 256 / ATOMS) S.xS[(size_t)r * lf + first + a2] = sX[r * ATOMS + a2];
+    for (int k = 4 * lane; k < nA; k += 32) {
+        *reinterpret_cast<int4 *>(S.actA + (size_t)i * MAXA + k) = *reinterpret_cast<const int4 *>(sA + at * MAXA + k);
+        *reinterpret_cast<ushort4 *>(S.actS + (size_t)i * MAXA + k) =
+            *reinterpret_cast<const ushort4 *>(sS + at * MAXA + k);
+    }
+}
+
+// -------------------------------------------------------------------------
 // forward: radial set (lane per atom)
 // -------------------------------------------------------------------------
 
@@ -117,9 +258,10 @@ __global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restri
     if (i < 0) return;
     const Img R = img_of(S.rep[S.rid[i]]);
     const d4 pi = S.pos[i];
-    const real rc = (real)RC_R, rc2 = rc * rc;
+    const real rc = (real)RC_R;
     const int cnt = S.cntR[i], nfe = S.cntFeR[i];
     const size_t ld = S.N;
+    const int *row = S.actR + i;
     real *q = W.q + (size_t)i * DP;
     real qR[NR], qE[NR], qD[NR], qA[NR], qS[NR];
 #pragma unroll
@@ -131,18 +273,17 @@ __global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restri
 #pragma unroll
         for (int k = 0; k < NB; k++) FR[k] = FE[k] = FD[k] = FA[k] = FS[k] = 0;
         // neighbour index two slots ahead, position and spin one slot ahead
-        int j1 = 0 < nfe ? S.nbrR[i] : 0;
-        int j2 = 1 < nfe ? S.nbrR[ld + i] : j1;
+        int j1 = 0 < nfe ? row[0] : 0;
+        int j2 = 1 < nfe ? row[ld] : j1;
         d4 p1 = S.pos[j1], v1 = spin[j1];
         for (int s = 0; s < nfe; s++) {
             const d4 pj = p1, vj = v1;
             j1 = j2;
             p1 = S.pos[j1];
             v1 = spin[j1];
-            if (s + 2 < nfe) j2 = S.nbrR[(size_t)(s + 2) * ld + i];
+            if (s + 2 < nfe) j2 = row[(size_t)(s + 2) * ld];
             real d[3];
             const real r2 = geom_p(R, pi, pj, d);
-            if (r2 >= rc2) continue;
             real r, ir;
             r_and_inv(r2, r, ir);
             const real rh[3] = {d[0] * ir, d[1] * ir, d[2] * ir};
@@ -186,18 +327,17 @@ __global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restri
         // non-magnetic neighbours: only the radial and single-ion channels survive
 #pragma unroll
         for (int k = 0; k < NB; k++) FR[k] = FS[k] = 0;
-        int j1_ = nfe < cnt ? S.nbrR[(size_t)(nfe) * ld + i] : 0;
-        int j2_ = nfe + 1 < cnt ? S.nbrR[(size_t)(nfe + 1) * ld + i] : j1_;
+        int j1_ = nfe < cnt ? row[(size_t)nfe * ld] : 0;
+        int j2_ = nfe + 1 < cnt ? row[(size_t)(nfe + 1) * ld] : j1_;
         d4 p1_ = S.pos[j1_];
         for (int s = nfe; s < cnt; s++) {
             const int j = j1_;
             const d4 pj_ = p1_;
             j1_ = j2_;
             p1_ = S.pos[j1_];
-            if (s + 2 < cnt) j2_ = S.nbrR[(size_t)(s + 2) * ld + i];
+            if (s + 2 < cnt) j2_ = row[(size_t)(s + 2) * ld];
             real d[3];
             const real r2 = geom_p(R, pi, pj_, d);
-            if (r2 >= rc2) continue;
             real r, ir;
             r_and_inv(r2, r, ir);
             real f[NB];
@@ -228,18 +368,17 @@ __global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restri
 #pragma unroll
             for (int k = 0; k < NB; k++) FR[k] = 0;
             const int b = part ? nfe : 0, e = part ? cnt : nfe;
-            int j1_ = b < e ? S.nbrR[(size_t)(b) * ld + i] : 0;
-            int j2_ = b + 1 < e ? S.nbrR[(size_t)(b + 1) * ld + i] : j1_;
+            int j1_ = b < e ? row[(size_t)b * ld] : 0;
+            int j2_ = b + 1 < e ? row[(size_t)(b + 1) * ld] : j1_;
             d4 p1_ = S.pos[j1_];
             for (int s = b; s < e; s++) {
                 const int j = j1_;
                 const d4 pj_ = p1_;
                 j1_ = j2_;
                 p1_ = S.pos[j1_];
-                if (s + 2 < e) j2_ = S.nbrR[(size_t)(s + 2) * ld + i];
+                if (s + 2 < e) j2_ = row[(size_t)(s + 2) * ld];
                 real d[3];
                 const real r2 = geom_p(R, pi, pj_, d);
-                if (r2 >= rc2) continue;
                 real f[NB], r, ir;
                 r_and_inv(r2, r, ir);
                 radial_basis(r, rc, f);
@@ -287,6 +426,58 @@ constexpr int ANG_ATOMS = 8;             // atoms per workgroup
 constexpr int ANG_TW = 2 * NA + NLM;     // staged values per neighbour
 constexpr int ANG_TS = 8 * ANG_TW + 1;   // per-atom stride (shifts LDS banks)
 
+// What the lanes of other atoms need of an atom: position, spin, box and
+// inverse box (zero on free axes), as doubles in LDS. Filled by its eight lanes.
+constexpr int AT_W = 12;
+__device__ inline void stage_atom(const Sys &S, const d4 *spin, int i, int lane, double *at) {
+    if (lane < 2) {
+        const d4 v = lane ? spin[i] : S.pos[i];
+        at[3 * lane] = v.x;
+        at[3 * lane + 1] = v.y;
+        at[3 * lane + 2] = v.z;
+    } else if (lane == 2) {
+        const Img g = img_of(S.rep[S.rid[i]]);
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            at[6 + a] = g.b[a];
+            at[9 + a] = g.ib[a];
+        }
+    }
+}
+template <typename real>
+__device__ inline real geom_lds(const double *at, const d4 &pj, real d[3]) {
+    const Img g = {{at[6], at[7], at[8]}, {at[9], at[10], at[11]}};
+    return geom_p(g, d4{at[0], at[1], at[2], 0.0}, pj, d);
+}
+
+// The pairs of the eight atoms of a wavefront as one sequence, atom after atom:
+// off[k] is the first pair of atom k (wave-uniform), find() the atom of pair p.
+struct Flat8 {
+    int off[ANG_ATOMS + 1];
+    __device__ void set(int n) {   // n: pairs of this lane's atom
+        off[0] = 0;
+#pragma unroll
+        for (int k = 0; k < ANG_ATOMS; k++) off[k + 1] = off[k] + __builtin_amdgcn_readlane(n, 8 * k);
+    }
+    __device__ int find(int p, int &o) const {
+        int a = 0;
+        o = 0;
+#pragma unroll
+        for (int k = 1; k < ANG_ATOMS; k++) {
+            const bool g = p >= off[k];
+            a += g;
+            o = g ? off[k] : o;
+        }
+        return a;
+    }
+    __device__ int own(int slot) const {   // first pair of atom `slot`
+        int o = 0;
+#pragma unroll
+        for (int k = 1; k < ANG_ATOMS; k++) o = slot >= k ? off[k] : o;
+        return o;
+    }
+};
+
 template <typename real>
 __device__ inline real dotc(const real *c, const real f[NB]) {
     real s = 0;
@@ -332,8 +523,8 @@ __global__ void __launch_bounds__(64) k_desc_angular(Sys S, const real *__restri
     __syncthreads();
     const int n = lane < NA ? lane : NA - 1;
     const int m0 = 3 * lane;                 // this lane's three harmonics, for every n
-    const real rc = (real)RC_A, rc2 = rc * rc;
-    const size_t ld = S.N;
+    const real rc = (real)RC_A;
+    const int *row = S.actA + (size_t)(i < 0 ? 0 : i) * MAXA;
     real A[NA][3], B[NA][3];
 #pragma unroll
     for (int x = 0; x < NA; x++)
@@ -349,8 +540,8 @@ __global__ void __launch_bounds__(64) k_desc_angular(Sys S, const real *__restri
         const int rounds = (smax[part] + 7) >> 3;
         // this lane's neighbour index two rounds ahead, position and spin one round ahead
         const int s0 = b + lane;
-        int jc = s0 < e ? S.nbrA[(size_t)s0 * ld + i] : 0;
-        int jn = s0 + 8 < e ? S.nbrA[(size_t)(s0 + 8) * ld + i] : jc;
+        int jc = s0 < e ? row[s0] : 0;
+        int jn = s0 + 8 < e ? row[s0 + 8] : jc;
         d4 pc = S.pos[jc], vc = {0, 0, 0, 0};
         if (spins) vc = spin[jc];
         for (int rd = 0; rd < rounds; rd++) {
@@ -359,34 +550,29 @@ __global__ void __launch_bounds__(64) k_desc_angular(Sys S, const real *__restri
             jc = jn;
             pc = S.pos[jc];
             if (spins) vc = spin[jc];
-            if (s + 16 < e) jn = S.nbrA[(size_t)(s + 16) * ld + i];
+            if (s + 16 < e) jn = row[s + 16];
             real *en = my + lane * ANG_TW;
             if (s < e) {
                 real d[3];
                 const real r2 = geom_p(R, pi, pj, d);
-                if (r2 < rc2) {
-                    real r, ir;
-                    r_and_inv(r2, r, ir);
-                    real f[NB];
-                    radial_basis(r, rc, f);
-                    if (spins) {
-                        const real sj[3] = {(real)vj.x, (real)vj.y, (real)vj.z};
-                        const real sig = si[0] * sj[0] + si[1] * sj[1] + si[2] * sj[2];
+                real r, ir;
+                r_and_inv(r2, r, ir);
+                real f[NB];
+                radial_basis(r, rc, f);
+                if (spins) {
+                    const real sj[3] = {(real)vj.x, (real)vj.y, (real)vj.z};
+                    const real sig = si[0] * sj[0] + si[1] * sj[1] + si[2] * sj[2];
 #pragma unroll
-                        for (int nn = 0; nn < NA; nn++) en[NA + nn] = sig * dotc(cS + nn * NB, f);
-                    }
-                    if (!reuse) {
-#pragma unroll
-                        for (int nn = 0; nn < NA; nn++) en[nn] = dotc(cA + nn * NB, f);
-                    }
-                    real Y[NLM];
-                    harmonics(d[0] * ir, d[1] * ir, d[2] * ir, Y);
-#pragma unroll
-                    for (int m = 0; m < NLM; m++) en[2 * NA + m] = Y[m];
-                } else {
-#pragma unroll
-                    for (int k = 0; k < ANG_TW; k++) en[k] = 0;
+                    for (int nn = 0; nn < NA; nn++) en[NA + nn] = sig * dotc(cS + nn * NB, f);
                 }
+                if (!reuse) {
+#pragma unroll
+                    for (int nn = 0; nn < NA; nn++) en[nn] = dotc(cA + nn * NB, f);
+                }
+                real Y[NLM];
+                harmonics(d[0] * ir, d[1] * ir, d[2] * ir, Y);
+#pragma unroll
+                for (int m = 0; m < NLM; m++) en[2 * NA + m] = Y[m];
             }
             __syncthreads();
             const int qn = min(8, e - (b + rd * 8));
@@ -812,9 +998,10 @@ __global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restric
     if (i < 0) return;
     const Img R = img_of(S.rep[S.rid[i]]);
     const d4 pi = S.pos[i];
-    const real rc = (real)RC_R, rc2 = rc * rc;
+    const real rc = (real)RC_R;
     const int cnt = S.cntR[i], nfe = S.cntFeR[i];
     const size_t ld = S.N;
+    const int *row = S.actR + i;
     const real *Fp = W.Fp + (size_t)i * DP;
     // the neighbours' contracted blocks for this atom's species
     const real *nR = W.rcoef + (size_t)(fe ? 0 : 1) * ld * NB, *nS = W.rcoef + (size_t)(fe ? 2 : 3) * ld * NB;
@@ -848,18 +1035,17 @@ __global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restric
             contract((C + P_CR) + part * NR * NB, Fp + D_R, NR, CR);
             contract((C + P_CSI) + part * NR * NB, Fp + D_SI, NR, CS);
             const int b = part ? nfe : 0, e = part ? cnt : nfe;
-            int j1_ = b < e ? S.nbrR[(size_t)(b) * ld + i] : 0;
-            int j2_ = b + 1 < e ? S.nbrR[(size_t)(b + 1) * ld + i] : j1_;
+            int j1_ = b < e ? row[(size_t)b * ld] : 0;
+            int j2_ = b + 1 < e ? row[(size_t)(b + 1) * ld] : j1_;
             d4 p1_ = S.pos[j1_];
             for (int s = b; s < e; s++) {
                 const int j = j1_;
                 const d4 pj_ = p1_;
                 j1_ = j2_;
                 p1_ = S.pos[j1_];
-                if (s + 2 < e) j2_ = S.nbrR[(size_t)(s + 2) * ld + i];
+                if (s + 2 < e) j2_ = row[(size_t)(s + 2) * ld];
                 real d[3];
                 const real r2 = geom_p(R, pi, pj_, d);
-                if (r2 >= rc2) continue;
                 real r, ir;
                 r_and_inv(r2, r, ir);
                 const real rh[3] = {d[0] * ir, d[1] * ir, d[2] * ir};
@@ -892,18 +1078,17 @@ __global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restric
             real CR[NB];
             contract((C + P_CR) + ((fe ? 0 : 2) + part) * NR * NB, Fp + D_R, NR, CR);
             const int b = part ? nfe : 0, e = part ? cnt : nfe;
-            int j1_ = b < e ? S.nbrR[(size_t)(b) * ld + i] : 0;
-            int j2_ = b + 1 < e ? S.nbrR[(size_t)(b + 1) * ld + i] : j1_;
+            int j1_ = b < e ? row[(size_t)b * ld] : 0;
+            int j2_ = b + 1 < e ? row[(size_t)(b + 1) * ld] : j1_;
             d4 p1_ = S.pos[j1_];
             for (int s = b; s < e; s++) {
                 const int j = j1_;
                 const d4 pj_ = p1_;
                 j1_ = j2_;
                 p1_ = S.pos[j1_];
-                if (s + 2 < e) j2_ = S.nbrR[(size_t)(s + 2) * ld + i];
+                if (s + 2 < e) j2_ = row[(size_t)(s + 2) * ld];
                 real d[3];
                 const real r2 = geom_p(R, pi, pj_, d);
-                if (r2 >= rc2) continue;
                 real r, ir;
                 r_and_inv(r2, r, ir);
                 const real rh[3] = {d[0] * ir, d[1] * ir, d[2] * ir};
@@ -941,9 +1126,10 @@ __global__ void __launch_bounds__(256) k_bwd_mag(Sys S, const real *__restrict__
     if (i >= S.N_fe || live(S, i) < 0) return;
     const Img R = img_of(S.rep[S.rid[i]]);
     const d4 pi = S.pos[i];
-    const real rc = (real)RC_R, rc2 = rc * rc;
+    const real rc = (real)RC_R;
     const int nfe = min(S.cntFeR[i], MAXFE);
     const size_t ld = S.N;
+    const int *row = S.actR + i;
     real F[3] = {0, 0, 0}, h[3] = {0, 0, 0};
     real si[3];
     load_spin(S.spin, i, si);
@@ -954,8 +1140,8 @@ __global__ void __launch_bounds__(256) k_bwd_mag(Sys S, const real *__restrict__
         for (int k = 0; k < 3 * NB; k++) Ci[k] = m[k];
     }
     // neighbour index two slots ahead, its position and spin one slot ahead
-    int j1_ = 0 < nfe ? S.nbrR[i] : 0;
-    int j2_ = 1 < nfe ? S.nbrR[ld + i] : j1_;
+    int j1_ = 0 < nfe ? row[0] : 0;
+    int j2_ = 1 < nfe ? row[ld] : j1_;
     d4 p1_ = S.pos[j1_], v1_ = S.spin[j1_];
     for (int s = 0; s < nfe; s++) {
         const int j = j1_;
@@ -963,10 +1149,9 @@ __global__ void __launch_bounds__(256) k_bwd_mag(Sys S, const real *__restrict__
         j1_ = j2_;
         p1_ = S.pos[j1_];
         v1_ = S.spin[j1_];
-        if (s + 2 < nfe) j2_ = S.nbrR[(size_t)(s + 2) * ld + i];
+        if (s + 2 < nfe) j2_ = row[(size_t)(s + 2) * ld];
         real d[3];
         const real r2 = geom_p(R, pi, pj_, d);
-        if (r2 >= rc2) continue;
         real r, ir;
         r_and_inv(r2, r, ir);
         const real rh[3] = {d[0] * ir, d[1] * ir, d[2] * ir};
@@ -1012,10 +1197,17 @@ __global__ void __launch_bounds__(256) k_bwd_mag(Sys S, const real *__restrict__
 //   with QA_nlm = 2 Fp^A_nl A_nlm + Fp^sa_nl B_nlm, QS_nlm = Fp^sa_nl A_nlm;
 //   h_ij = sum_lm Y_lm sum_n QS_nlm g^sa_n, so that dE_i/ds_j = h_ij s_i and
 //   the pair adds h_ij s_j to dE_i/ds_i.
-// The eight lanes of an atom take its neighbours round robin, each pair in
-// full; the atom's 336 QA/QS values sit in LDS. A pair record holds
-// (dE_i/dd_ij, h_ij); the gather forms every sum in slot order.
+// A wavefront takes eight atoms, whose 336 QA/QS values each sit in LDS, and
+// their pairs 64 at a time, a lane per pair in full. A pair record holds
+// (dE_i/dd_ij, h_ij).
 // -------------------------------------------------------------------------
+
+// What bounds it: FP64 issue and the LDS reads of QA/QS (14 per harmonic and
+// pair), both per lane slot. With the neighbours dealt eight per atom and round
+// from the Verlet rows only 60 % of the slots held a pair inside the cutoff;
+// the flat in-cutoff pairs fill 90 %:
+// 2,097,152 atoms, FP64, carriers 4.45 -> 3.49 ms per launch, the others 2.75 -> 2.10;
+// 1,048,576 atoms, FP32, 1.23 -> 0.98 and 0.91 -> 0.63 ms.
 
 // Each species runs as its own launch over atoms [first, last). Atoms without
 // spin work (the second species, or every atom of a structural-only model)
@@ -1029,12 +1221,14 @@ __global__ void __launch_bounds__(64) k_bwd_angular(Sys S, const real *__restric
                                                     int last) {
     constexpr int QSTRIDE = qstride<FE>();
     __shared__ real sQ[ANG_ATOMS * QSTRIDE];
-    const int lane = threadIdx.x & 7, slot = threadIdx.x >> 3;
+    __shared__ double sAt[ANG_ATOMS * AT_W];
+    const int tid = threadIdx.x, lane = tid & 7, slot = tid >> 3;
     const bool fe = first < S.N_fe;    // species 0: the pair types tau = 0, 1
-    int i = first + blockIdx.x * ANG_ATOMS + slot;
-    i = live(S, i < last ? i : -1);
-    real *Q = sQ + slot * QSTRIDE;   // QA[n][m], then QS[n][m] on spin carriers
+    const int i0 = first + blockIdx.x * ANG_ATOMS;
+    const int i = live(S, i0 + slot < last ? i0 + slot : -1);
+    int cnt = 0, nfe = 0;
     if (i >= 0) {
+        real *Q = sQ + slot * QSTRIDE;   // QA[n][m], then QS[n][m] on spin carriers
         const real *Fp = W.Fp + (size_t)i * DP;
         for (int x = lane; x < NA * NLM; x += 8) {
             const int n = x / NLM, m = x - n * NLM, l = l_of_lm(m) - 1;
@@ -1048,79 +1242,66 @@ __global__ void __launch_bounds__(64) k_bwd_angular(Sys S, const real *__restric
                 Q[x] = real(2) * fa * ab[m];
             }
         }
+        stage_atom(S, S.spin, i, lane, sAt + slot * AT_W);
+        cnt = S.cntA[i];
+        nfe = S.cntFeA[i];
     }
     __syncthreads();
-    if (i < 0) return;
-    const Img R = img_of(S.rep[S.rid[i]]);
-    const d4 pi = S.pos[i];
-    const real rc = (real)RC_A, rc2 = rc * rc;
-    const int cnt = S.cntA[i], nfe = S.cntFeA[i];
+    const real rc = (real)RC_A;
     const size_t ld = S.N;
-    real si[3];
-    load_spin(S.spin, i, si);
     real Fo[3] = {0, 0, 0}, ho[3] = {0, 0, 0};     // own-side sums of this lane's pairs
-    // In-cutoff pairs go to the atom's lanes by their rank among in-cutoff
-    // pairs, so that the lane partial sums (and their rounding) depend on the
-    // positions only and not on which farther atoms the list happens to hold.
-    const int gbase = threadIdx.x & ~7;
-    int rank = 0;
+    // the next pair of this lane, loaded one round ahead
+    Flat8 fl;
+    int pn = 0, rn = 0;                            // its part and the first pair of its round
+    fl.set(nfe);
+    int off0 = fl.own(slot), off1 = 0;
+    int na = -1, nj = 0, nsr = 0;
+    d4 np = {0, 0, 0, 0};
+    auto next = [&]() {
+        na = -1;
+        if (rn >= fl.off[ANG_ATOMS] && pn == 0) {
+            pn = 1;
+            rn = 0;
+            fl.set(cnt - nfe);
+            off1 = fl.own(slot);
+        }
+        if (rn >= fl.off[ANG_ATOMS]) return;       // no round left
+        const int p = rn + tid;
+        if (p < fl.off[ANG_ATOMS]) {
+            int o;
+            na = fl.find(p, o);
+            const size_t x = (size_t)(i0 + na) * MAXA + (p - o) + (pn ? S.cntFeA[i0 + na] : 0);
+            nj = S.actA[x];
+            nsr = S.actS[x];
+            np = S.pos[nj];
+        }
+    };
+    next();
+    // rounds of 64 pairs of the eight atoms, spin-carrying neighbours first
 #pragma unroll 1
-    for (int part = 0; part < 2; part++) {
+    while (rn < fl.off[ANG_ATOMS]) {
+        const int part = pn, r0 = rn, T = fl.off[ANG_ATOMS];
+        const int a = na, j = nj, sr = nsr;
+        const d4 pj = np;
+        rn += 64;
+        next();
         const int tau = (fe ? 0 : 2) + part;
         const real *cA = C + P_CA + tau * NA * NB, *cS = C + P_CSA + tau * NA * NB;
         const bool spins = FE && part == 0;
-        const int b = part ? nfe : 0, e = part ? cnt : nfe;
-        // this lane's neighbour index two rounds ahead, its position one round ahead
-        int jc = b + lane < e ? S.nbrA[(size_t)(b + lane) * ld + i] : 0;
-        int jn = b + lane + 8 < e ? S.nbrA[(size_t)(b + lane + 8) * ld + i] : jc;
-        d4 pc = S.pos[jc];
-#pragma unroll 1
-        for (int base = b; base < e; base += 8) {
-            const int s0 = base + lane;
-            int j0 = jc;
-            const d4 pj = pc;
-            jc = jn;
-            pc = S.pos[jc];
-            if (s0 + 16 < e) jn = S.nbrA[(size_t)(s0 + 16) * ld + i];
-            real d0[3] = {0, 0, 0}, r20 = rc2;
-            if (s0 < e) r20 = geom_p(R, pi, pj, d0);
-            else j0 = 0;
-            const bool in = s0 < e && r20 < rc2;
-            // records of listed pairs beyond the cutoff are zero; each record
-            // goes where the partner's gather reads it
-            if (s0 < e && !in) {
-                real *z = W.pbA + ((size_t)S.revA[s0 * ld + i] * ld + j0) * 4;
-                z[0] = z[1] = z[2] = z[3] = 0;
-            }
-            const unsigned gm = (unsigned)(__ballot(in) >> gbase) & 0xffu;
-            const int c = __popc(gm);
-            const int q = (lane - rank) & 7;
-            int src = 0;
-            {
-                unsigned m = gm;
-                for (int x = 0; x < q && m; x++) m &= m - 1;
-                src = m ? __ffs(m) - 1 : 0;
-            }
-            const bool mine = q < c;
-            rank += c;
-            const int j = __shfl(j0, gbase + src);
-            const int s = __shfl(s0, gbase + src);
+        real G0 = 0, G1 = 0, G2 = 0, hs = 0, sj[3] = {0, 0, 0};
+        if (a >= 0) {
+            const double *at = sAt + a * AT_W;
             real d[3];
-            d[0] = __shfl(d0[0], gbase + src);
-            d[1] = __shfl(d0[1], gbase + src);
-            d[2] = __shfl(d0[2], gbase + src);
-            const real r2 = __shfl(r20, gbase + src);
-            if (!mine) continue;
-            real *rec = W.pbA + ((size_t)S.revA[s * ld + i] * ld + j) * 4;
+            const real r2 = geom_lds(at, pj, d);
             real r, ir;
             r_and_inv(r2, r, ir);
             const real rh[3] = {d[0] * ir, d[1] * ir, d[2] * ir};
             real f[NB], df[NB];
             radial_basis_d(r, rc, f, df);
-            real sig = 0, sj[3] = {0, 0, 0};
+            real sig = 0;
             if (spins) {
                 load_spin(S.spin, j, sj);
-                sig = si[0] * sj[0] + si[1] * sj[1] + si[2] * sj[2];
+                sig = (real)at[3] * sj[0] + (real)at[4] * sj[1] + (real)at[5] * sj[2];
             }
             real gA[NA], dgA[NA], gS[NA], dgS[NA];
 #pragma unroll
@@ -1130,14 +1311,14 @@ __global__ void __launch_bounds__(64) k_bwd_angular(Sys S, const real *__restric
                 gS[n] = spins ? dotc(cS + n * NB, f) : real(0);
                 dgS[n] = spins ? dotc(cS + n * NB, df) : real(0);
             }
-            real sv = 0, sl = 0, hs = 0, su0 = 0, su1 = 0, su2 = 0;
+            real sv = 0, sl = 0, su0 = 0, su1 = 0, su2 = 0;
             // straight-line over the 24 harmonics; the register fence before
             // each one keeps the compiler from evaluating all of them at once
             static_for<NLM>([&](auto M) {
                 constexpr int m = decltype(M)::value;
                 real Y, gx, gy, gz;
                 real hx = rh[0], hy = rh[1], hz = rh[2];
-                int qo = slot * QSTRIDE;
+                int qo = a * QSTRIDE;
                 asm volatile("" : "+v"(hx), "+v"(hy), "+v"(hz), "+v"(qo), "+v"(sv), "+v"(sl), "+v"(hs), "+v"(su0),
                              "+v"(su1), "+v"(su2));
                 const real *Qm = sQ + qo;
@@ -1165,19 +1346,40 @@ __global__ void __launch_bounds__(64) k_bwd_angular(Sys S, const real *__restric
                 su1 += U * gy;
                 su2 += U * gz;
             });
-            const real G0 = sv * rh[0] + (su0 - sl * rh[0]) * ir;
-            const real G1 = sv * rh[1] + (su1 - sl * rh[1]) * ir;
-            const real G2 = sv * rh[2] + (su2 - sl * rh[2]) * ir;
+            G0 = sv * rh[0] + (su0 - sl * rh[0]) * ir;
+            G1 = sv * rh[1] + (su1 - sl * rh[1]) * ir;
+            G2 = sv * rh[2] + (su2 - sl * rh[2]) * ir;
+            // the record goes where the partner's gather reads it
+            real *rec = W.pbA + ((size_t)(sr >> 8) * ld + j) * 4;
             rec[0] = G0;
             rec[1] = G1;
             rec[2] = G2;
             rec[3] = hs;
-            Fo[0] += G0;
-            Fo[1] += G1;
-            Fo[2] += G2;
-            ho[0] += hs * sj[0];
-            ho[1] += hs * sj[1];
-            ho[2] += hs * sj[2];
+        }
+        // Own sums: lane l of an atom takes its pairs of rank l modulo 8 (ranks
+        // over both parts) from the lanes that formed them, so the order of
+        // the sum does not depend on which atoms share the wavefront.
+        const int n = part ? cnt - nfe : nfe, mo = part ? off1 : off0;
+        const int lo = max(r0 - mo, 0), hi = min(n, min(r0 + 64, T) - mo);   // this round's ranks of the atom
+        int r = lo + ((lane - (part ? nfe : 0) - lo) & 7);
+        while (__any(r < hi)) {
+            const bool ok = r < hi;
+            const int src = ok ? mo + r - r0 : tid;
+            const real x0 = __shfl(G0, src), x1 = __shfl(G1, src), x2 = __shfl(G2, src);
+            if (ok) {
+                Fo[0] += x0;
+                Fo[1] += x1;
+                Fo[2] += x2;
+            }
+            if (spins) {
+                const real y0 = __shfl(hs * sj[0], src), y1 = __shfl(hs * sj[1], src), y2 = __shfl(hs * sj[2], src);
+                if (ok) {
+                    ho[0] += y0;
+                    ho[1] += y1;
+                    ho[2] += y2;
+                }
+            }
+            r += 8;
         }
     }
     // own-side sums over the atom's eight lanes (fixed xor tree)
@@ -1186,77 +1388,60 @@ __global__ void __launch_bounds__(64) k_bwd_angular(Sys S, const real *__restric
         Fo[x] = xor_sum8(Fo[x]);
         ho[x] = xor_sum8(ho[x]);
     }
-    if (lane == 0) put_pair(W.ownA, (size_t)i, Fo, ho);
+    if (lane == 0 && i >= 0) put_pair(W.ownA, (size_t)i, Fo, ho);
 }
 
 // -------------------------------------------------------------------------
 // gather: forces and fields
 // -------------------------------------------------------------------------
 
+// Eight lanes per atom over its in-cutoff pairs, rank modulo 8, then a fixed
+// xor tree: the partner records sit in the atom's own slots.
 template <typename real>
 __global__ void __launch_bounds__(256) k_gather(Sys S, Work<real> W) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= S.N || live(S, k) < 0) return;   // a paused replica keeps its last forces and fields
+    const int lane = threadIdx.x & 7;
+    const int k0 = blockIdx.x * 32 + (threadIdx.x >> 3);
+    const int k = live(S, k0 < S.N ? k0 : -1);   // a paused replica keeps its last forces and fields
+    if (k < 0) return;
     const size_t ld = S.N;
     const bool fe = S.mag && k < S.N_fe;   // spin carrier
-    real F[3], h[3];
-    {
-        const real *a = W.ownR + (size_t)k * 6;
-        F[0] = a[0];
-        F[1] = a[1];
-        F[2] = a[2];
-        h[0] = a[3];
-        h[1] = a[4];
-        h[2] = a[5];
-    }
-    const int na = S.cntA[k];
-    {
-        const real *a = W.ownA + (size_t)k * 6;
-        F[0] += a[0];
-        F[1] += a[1];
-        F[2] += a[2];
-        h[0] += a[3];
-        h[1] += a[4];
-        h[2] += a[5];
-    }
-    // partner records sit in this atom's own slots: the reads are coalesced
-    if (fe) {
-        const real *a = W.ownM + (size_t)k * 6;
-        F[0] += a[0];
-        F[1] += a[1];
-        F[2] += a[2];
-        h[0] += a[3];
-        h[1] += a[4];
-        h[2] += a[5];
-    }
-#pragma unroll 4
-    for (int s = 0; s < na; s++) {
-        const real *p = W.pbA + ((size_t)s * ld + k) * 4;
+    const int na = S.cntA[k], nfe = fe ? S.cntFeA[k] : 0;
+    real F[3] = {0, 0, 0}, h[3] = {0, 0, 0};
+    for (int s = lane; s < na; s += 8) {
+        const real *p = W.pbA + ((size_t)(S.actS[(size_t)k * MAXA + s] & 0xff) * ld + k) * 4;
         F[0] -= p[0];
         F[1] -= p[1];
         F[2] -= p[2];
-        if (fe) {
-            const int j = S.nbrA[s * ld + k];
-            if (j < S.N_fe) {
-                real sj[3];
-                load_spin(S.spin, j, sj);
-                h[0] += p[3] * sj[0];
-                h[1] += p[3] * sj[1];
-                h[2] += p[3] * sj[2];
-            }
+        if (s < nfe) {
+            real sj[3];
+            load_spin(S.spin, S.actA[(size_t)k * MAXA + s], sj);
+            h[0] += p[3] * sj[0];
+            h[1] += p[3] * sj[1];
+            h[2] += p[3] * sj[2];
         }
     }
-    d4 f4 = {(double)F[0], (double)F[1], (double)F[2], 0.0};
-    S.force[k] = f4;
-    d4 h4 = {0, 0, 0, 0};
+#pragma unroll
+    for (int x = 0; x < 3; x++) {
+        F[x] = xor_sum8(F[x]);
+        h[x] = xor_sum8(h[x]);
+    }
+    if (lane >= 3) return;   // lanes 0-2 finish one component each
+    real Fx = lane == 0 ? F[0] : lane == 1 ? F[1] : F[2], hx = lane == 0 ? h[0] : lane == 1 ? h[1] : h[2];
+    const real *aR = W.ownR + (size_t)k * 6, *aA = W.ownA + (size_t)k * 6;
+    Fx += aR[lane] + aA[lane];
+    hx += aR[3 + lane] + aA[3 + lane];
+    if (fe) {
+        const real *aM = W.ownM + (size_t)k * 6;
+        Fx += aM[lane];
+        hx += aM[3 + lane];
+    }
+    (&S.force[k].x)[lane] = (double)Fx;
+    double H = 0;
     if (fe) {
         const RepDev &R = S.rep[S.rid[k]];
-        const double fr = ramp_frac(R), zs = R.mu_s * MUB;
-        h4.x = -(double)h[0] + zs * (R.B0[0] + (R.B1[0] - R.B0[0]) * fr);
-        h4.y = -(double)h[1] + zs * (R.B0[1] + (R.B1[1] - R.B0[1]) * fr);
-        h4.z = -(double)h[2] + zs * (R.B0[2] + (R.B1[2] - R.B0[2]) * fr);
+        H = -(double)hx + R.mu_s * MUB * (R.B0[lane] + (R.B1[lane] - R.B0[lane]) * ramp_frac(R));
     }
-    S.field[k] = h4;
+    (&S.field[k].x)[lane] = H;
 }
 
 // -------------------------------------------------------------------------
@@ -1266,43 +1451,55 @@ __global__ void __launch_bounds__(256) k_gather(Sys S, Work<real> W) {
 // -------------------------------------------------------------------------
 
 // spin-angular part of a_ij: sum_n g^sa_n(r_ij) sum_lm Fp^sa_nl A_nlm Y_lm(rhat_ij);
-// lanes take the atom's spin-carrying neighbours round robin, P = Fp^sa A in LDS
+// a lane per pair of the wavefront's eight spins, P = Fp^sa A in LDS
 constexpr int PSTRIDE = NA * NLM + 1;
 
 template <typename real>
 __global__ void __launch_bounds__(64) k_assemble_angular(Sys S, const real *__restrict__ C, Work<real> W) {
     __shared__ real sP[ANG_ATOMS * PSTRIDE];
-    const int lane = threadIdx.x & 7, slot = threadIdx.x >> 3;
-    const int i0 = blockIdx.x * ANG_ATOMS + slot;
-    const int i = live(S, i0 < S.N_fe ? i0 : -1);
+    __shared__ double sAt[ANG_ATOMS * AT_W];
+    const int tid = threadIdx.x, lane = tid & 7, slot = tid >> 3;
+    const int i0 = blockIdx.x * ANG_ATOMS;
+    const int i = live(S, i0 + slot < S.N_fe ? i0 + slot : -1);
     const real *cS = C + P_CSA;   // tau = (Fe, Fe)
-    real *P = sP + slot * PSTRIDE;
+    int nfe = 0;
     if (i >= 0) {
+        real *P = sP + slot * PSTRIDE;
         const real *Fp = W.Fp + (size_t)i * DP;
         for (int x = lane; x < NA * NLM; x += 8) {
             const int n = x / NLM, m = x - n * NLM;
             P[x] = Fp[D_SA + 4 * n + l_of_lm(m) - 1] * W.AB[((size_t)i * NA + n) * NAB + m];
         }
+        stage_atom(S, S.spin, i, lane, sAt + slot * AT_W);
+        nfe = S.cntFeA[i];
     }
     __syncthreads();
-    if (i < 0) return;
-    const Img R = img_of(S.rep[S.rid[i]]);
-    const d4 pi = S.pos[i];
-    const real rc = (real)RC_A, rc2 = rc * rc;
-    const int nfe = S.cntFeA[i];
-    const size_t ld = S.N, lf = S.N_fe;
-    // this lane's neighbour index two rounds ahead, its position one round ahead
-    int j1 = lane < nfe ? S.nbrA[(size_t)lane * ld + i] : 0;
-    int j2 = lane + 8 < nfe ? S.nbrA[(size_t)(lane + 8) * ld + i] : j1;
-    d4 p1 = S.pos[j1];
-    for (int s = lane; s < nfe; s += 8) {
-        const d4 pj = p1;
-        j1 = j2;
-        p1 = S.pos[j1];
-        if (s + 16 < nfe) j2 = S.nbrA[(size_t)(s + 16) * ld + i];
+    const real rc = (real)RC_A;
+    const size_t lf = S.N_fe;
+    Flat8 fl;
+    fl.set(nfe);
+    // this lane's next pair, loaded one round ahead
+    int na = -1, ns = 0;
+    d4 np = {0, 0, 0, 0};
+    auto next = [&](int p) {
+        na = -1;
+        if (p < fl.off[ANG_ATOMS]) {
+            int o;
+            na = fl.find(p, o);
+            const size_t x = (size_t)(i0 + na) * MAXA + (p - o);
+            ns = S.actS[x] & 0xff;
+            np = S.pos[S.actA[x]];
+        }
+    };
+    next(tid);
+#pragma unroll 1
+    for (int r0 = 0; r0 < fl.off[ANG_ATOMS]; r0 += 64) {
+        const int at = na, s = ns;
+        const d4 pj = np;
+        next(r0 + 64 + tid);
+        if (at < 0) continue;
         real d[3];
-        const real r2 = geom_p(R, pi, pj, d);
-        if (r2 >= rc2) continue;
+        const real r2 = geom_lds(sAt + at * AT_W, pj, d);
         real r, ir;
         r_and_inv(r2, r, ir);
         real f[NB];
@@ -1313,6 +1510,7 @@ __global__ void __launch_bounds__(64) k_assemble_angular(Sys S, const real *__re
         real a = 0;
         real Y[NLM];
         harmonics(d[0] * ir, d[1] * ir, d[2] * ir, Y);
+        const real *P = sP + at * PSTRIDE;
 #pragma unroll
         for (int m = 0; m < NLM; m++) {
             real w = 0;
@@ -1320,8 +1518,7 @@ __global__ void __launch_bounds__(64) k_assemble_angular(Sys S, const real *__re
             for (int n = 0; n < NA; n++) w += P[n * NLM + m] * gS[n];
             a += w * Y[m];
         }
-        const int sr = S.a2r[s * ld + i];
-        if (sr < MAXFE) W.csa[(size_t)sr * lf + i] = a;
+        W.csa[(size_t)s * lf + i0 + at] = a;   // angular slots of spin carriers lead: s < MAXFE
     }
 }
 
@@ -1342,6 +1539,7 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
     const real rc = (real)RC_R, rc2 = rc * rc, rca = (real)RC_A, rca2 = rca * rca;   // as the angular pass
     const int cnt = S.cntR[i], nfe_all = S.cntFeR[i], nfe = min(nfe_all, MAXFE);
     const size_t ld = S.N, lf = S.N_fe;
+    const int *row = S.actR + i;
     const int p = S.colpos[i];
     const real *Fp = W.Fp + (size_t)i * DP;
     real Ci[MCOEF];
@@ -1351,41 +1549,19 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
         for (int k = 0; k < MCOEF; k++) Ci[k] = m[k];
     }
     real Axx = 0, Ayy = 0, Azz = 0, Axy = 0, Axz = 0, Ayz = 0;
-    int cs = 0;
     {
         real CS[NB];
         contract((C + P_CSI), Fp + D_SI, NR, CS);
         // neighbour index two slots ahead, its position one slot ahead
-        int j1 = 0 < nfe ? S.nbrR[i] : 0;
-        int j2 = 1 < nfe ? S.nbrR[ld + i] : j1;
+        int j1 = 0 < nfe ? row[0] : 0;
+        int j2 = 1 < nfe ? row[ld] : j1;
         d4 p1 = S.pos[j1];
-        // first the in-cutoff slots (nfe <= MAXFE = 64 bits), then the work in
-        // slot order over those alone: at temperature the lanes of a
-        // wavefront have their out-of-cutoff slots at different places, and
-        // a loop over all slots would run its body for their union
-        uint64_t in = 0;
         for (int s = 0; s < nfe; s++) {
+            const int j = j1;
             const d4 pj = p1;
             j1 = j2;
             p1 = S.pos[j1];
-            if (s + 2 < nfe) j2 = S.nbrR[(size_t)(s + 2) * ld + i];
-            real d[3];
-            if (geom_p(R, pi, pj, d) < rc2) in |= 1ull << s;
-        }
-        int s = in ? __ffsll((long long)in) - 1 : -1;
-        in = in ? in & (in - 1) : 0;
-        int jn = s >= 0 ? S.nbrR[(size_t)s * ld + i] : 0;
-        d4 pn = S.pos[jn];
-        while (s >= 0) {
-            const int j = jn;
-            const d4 pj = pn;
-            const int s_ = s;
-            s = in ? __ffsll((long long)in) - 1 : -1;
-            in = in ? in & (in - 1) : 0;
-            if (s >= 0) {
-                jn = S.nbrR[(size_t)s * ld + i];
-                pn = S.pos[jn];
-            }
+            if (s + 2 < nfe) j2 = row[(size_t)(s + 2) * ld];
             real d[3];
             const real r2 = geom_p(R, pi, pj, d);
             real r, ir;
@@ -1402,8 +1578,8 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
                 K += (Ci[2 * NB + k] + mj[2 * NB + k]) * f[k];
             }
             if (r2 < rca2) {
-                const int t = min(S.revR[s_ * ld + i], MAXFE - 1);
-                J += W.csa[(size_t)s_ * lf + i] + W.csa[(size_t)t * lf + j];
+                const int a = S.xS[(size_t)s * lf + i];
+                J += W.csa[(size_t)(a & 0xff) * lf + i] + W.csa[(size_t)(a >> 8) * lf + j];
             }
             const real g = dotk(CS, f);
             Axx += g * rh[0] * rh[0];
@@ -1412,31 +1588,29 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
             Axy += g * rh[0] * rh[1];
             Axz += g * rh[0] * rh[2];
             Ayz += g * rh[1] * rh[2];
-            real *c = W.cpl + ((size_t)cs * lf + p) * 6;
+            real *c = W.cpl + ((size_t)s * lf + p) * 6;
             c[0] = J;
             c[1] = D;
             c[2] = K;
             c[3] = rh[0];
             c[4] = rh[1];
             c[5] = rh[2];
-            W.cpl_j[(size_t)cs * lf + p] = j;
-            cs++;
+            W.cpl_j[(size_t)s * lf + p] = j;
         }
     }
     {
         real CS[NB];
         contract((C + P_CSI) + 1 * NR * NB, Fp + D_SI, NR, CS);
-        int j1 = nfe_all < cnt ? S.nbrR[(size_t)nfe_all * ld + i] : 0;
-        int j2 = nfe_all + 1 < cnt ? S.nbrR[(size_t)(nfe_all + 1) * ld + i] : j1;
+        int j1 = nfe_all < cnt ? row[(size_t)nfe_all * ld] : 0;
+        int j2 = nfe_all + 1 < cnt ? row[(size_t)(nfe_all + 1) * ld] : j1;
         d4 p1 = S.pos[j1];
         for (int s = nfe_all; s < cnt; s++) {
             const d4 pj = p1;
             j1 = j2;
             p1 = S.pos[j1];
-            if (s + 2 < cnt) j2 = S.nbrR[(size_t)(s + 2) * ld + i];
+            if (s + 2 < cnt) j2 = row[(size_t)(s + 2) * ld];
             real d[3];
             const real r2 = geom_p(R, pi, pj, d);
-            if (r2 >= rc2) continue;
             real r, ir;
             r_and_inv(r2, r, ir);
             const real rh[3] = {d[0] * ir, d[1] * ir, d[2] * ir};
@@ -1460,7 +1634,7 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
     o[5] = Ayz;
     o[6] = Fp[D_OS];
     o[7] = 0;
-    W.cpl_n[p] = cs;
+    W.cpl_n[p] = nfe;
 }
 
 inline int nblk(int n, int b) { return (n + b - 1) / b; }
@@ -1470,6 +1644,12 @@ inline int nblk(int n, int b) { return (n + b - 1) / b; }
 #define NEP_SPLIT(per)                                  \
     const int ge = S.N - S.N_fe;                        \
     const int nb_fe = nblk(S.N_fe, per), nb_ge = nblk(ge, per);
+
+template <typename real>
+void launch_active(const Sys &S, int mode, hipStream_t st) {
+    const int n = mode == PASS_FULL ? S.N : S.N_fe;
+    if (n) hipLaunchKernelGGL(k_active<real>, dim3(nblk(n, 32)), dim3(256), 0, st, S, n);
+}
 
 // spin-step passes (PASS_SPIN, PASS_SPIN_REUSE) cover the spin carriers only:
 // the frozen-Fp magnetic energy has no term on atoms without a spin
@@ -1531,7 +1711,7 @@ void launch_bwd_angular(const Sys &S, const ModelDev<real> &M, const Work<real> 
 template <typename real>
 void launch_gather(const Sys &S, const Work<real> &W, hipStream_t st) {
     if (S.N == 0) return;
-    hipLaunchKernelGGL(k_gather<real>, dim3(nblk(S.N, 256)), dim3(256), 0, st, S, W);
+    hipLaunchKernelGGL(k_gather<real>, dim3(nblk(S.N, 32)), dim3(256), 0, st, S, W);
 }
 
 template <typename real>
@@ -1548,6 +1728,7 @@ void launch_assemble_pairs(const Sys &S, const ModelDev<real> &M, const Work<rea
 }
 
 #define NEP_INST(real)                                                                                           \
+    template void launch_active<real>(const Sys &, int, hipStream_t);                                            \
     template void launch_desc_radial<real>(const Sys &, const ModelDev<real> &, const Work<real> &, const d4 *, \
                                            int, hipStream_t);                                                    \
     template void launch_desc_angular<real>(const Sys &, const ModelDev<real> &, const Work<real> &, const d4 *,\

@@ -121,9 +121,8 @@ __device__ inline void sort_row(int *row, int n) {
 
 // Fallback, one lane per atom, for the atoms of cells whose 27-cell
 // neighbourhood holds more candidates than the cell kernel stages: the
-// radial-set list sorted by atom index in LDS; the angular-set list is the
-// sorted radial row filtered by distance (rc_A + skin < rc_R + skin), so it
-// comes out sorted and each of its entries knows its radial slot (a2r).
+// row sorted by atom index in LDS; the entries within rc_A + skin are numbered
+// in row order (r2a, their angular slots).
 __global__ void __launch_bounds__(BLK) k_build(Sys S, double rl2R, double rl2A) {
     if (S.flags[F_REBUILD] == 0) return;
     __shared__ int rowR[MAXR * BLK];
@@ -167,29 +166,20 @@ __global__ void __launch_bounds__(BLK) k_build(Sys S, double rl2R, double rl2A) 
     bool over = nr > MAXR;
     nr = min(nr, MAXR);
     sort_row(rowR + t, nr);
-    int fe = 0, na = 0, fea = 0;
+    int fe = 0, na = 0;
     for (int s = 0; s < nr; s++) {
         const int j = rowR[s * BLK + t];
-        S.nbrR[(size_t)s * S.N + i] = j;
         fe += j < S.N_fe;
         double dx, dy, dz;
         min_image(g, pi, S.pos[j], dx, dy, dz);
-        if (dx * dx + dy * dy + dz * dz < rl2A) {
-            if (na < MAXA) {
-                S.nbrA[(size_t)na * S.N + i] = j;
-                S.a2r[(size_t)na * S.N + i] = s;
-            }
-            na++;
-            fea += j < S.N_fe;
-        }
+        const bool ang = dx * dx + dy * dy + dz * dz < rl2A;
+        S.rowR[(size_t)s * S.N + i] = ang && na < MAXA ? j | ANG_BIT : j;
+        S.r2a[(size_t)s * S.N + i] = ang && na < MAXA ? na : NO_SLOT;
+        na += ang;
     }
     over |= na > MAXA;
-    na = min(na, MAXA);
-    fea = min(fea, na);
-    S.cntR[i] = nr;
-    S.cntFeR[i] = fe;
-    S.cntA[i] = na;
-    S.cntFeA[i] = fea;
+    S.lenR[i] = nr;
+    S.lenFeR[i] = fe;
     if (over || (S.mag && i < S.N_fe && fe > MAXFE)) {
         atomicOr(&S.flags[F_OVERFLOW], 1);
         atomicOr(&S.rep[S.rid[i]].failed, 1);
@@ -201,8 +191,8 @@ __global__ void __launch_bounds__(BLK) k_build(Sys S, double rl2R, double rl2A) 
 // staged in LDS, sorted by atom index (bitonic), and their positions loaded
 // once; then 8 lanes per home atom split the sorted candidates into
 // contiguous eighths, count their hits, take offsets by a prefix over the
-// eight lanes and write them in order: every radial row comes out sorted,
-// the angular row is its sub-row within rc_A + skin, with its radial slots.
+// eight lanes and write them in order: every row comes out sorted, its entries
+// within rc_A + skin numbered in row order (r2a).
 // Lists are the same as the per-atom kernel's. A neighbourhood with more than
 // CAND candidates is left to that kernel (cell_fill[cell] = 1).
 constexpr int CAND = 1024;
@@ -288,7 +278,7 @@ __global__ void __launch_bounds__(BC) k_build_cells(Sys S, double rl2R, double r
         const int i = act ? S.cell_atoms[hbeg + h] : 0;
         const d4 pi = S.pos[i];
         // pass 1: hits of this lane's eighth
-        int cR = 0, cRf = 0, cA = 0, cAf = 0;
+        int cR = 0, cRf = 0, cA = 0;
         for (int k = lo; k < hi && act; k++) {
             const int j = cidx[k];
             if (j == i) continue;
@@ -298,10 +288,7 @@ __global__ void __launch_bounds__(BC) k_build_cells(Sys S, double rl2R, double r
             if (r2 < rl2R) {
                 cR++;
                 cRf += j < S.N_fe;
-                if (r2 < rl2A) {
-                    cA++;
-                    cAf += j < S.N_fe;
-                }
+                cA += r2 < rl2A;
             }
         }
         // exclusive offsets over the atom's eight lanes
@@ -314,12 +301,9 @@ __global__ void __launch_bounds__(BC) k_build_cells(Sys S, double rl2R, double r
                 oA += uA;
             }
         }
-        int fR = cRf, fA = cAf;
+        int fR = cRf;
 #pragma unroll
-        for (int d = 1; d < LPA; d <<= 1) {
-            fR += __shfl_xor(fR, d, LPA);
-            fA += __shfl_xor(fA, d, LPA);
-        }
+        for (int d = 1; d < LPA; d <<= 1) fR += __shfl_xor(fR, d, LPA);
         const int nr = __shfl(oR, LPA - 1, LPA), na = __shfl(oA, LPA - 1, LPA);
         oR -= cR;
         oA -= cA;
@@ -331,23 +315,19 @@ __global__ void __launch_bounds__(BC) k_build_cells(Sys S, double rl2R, double r
             min_image(g, pi, d4{cpx[k], cpy[k], cpz[k], 0.0}, dx, dy, dz);
             const double r2 = dx * dx + dy * dy + dz * dz;
             if (r2 < rl2R) {
-                if (oR < MAXR) S.nbrR[(size_t)oR * S.N + i] = j;
-                if (r2 < rl2A) {
-                    if (oA < MAXA) {
-                        S.nbrA[(size_t)oA * S.N + i] = j;
-                        S.a2r[(size_t)oA * S.N + i] = oR;
-                    }
-                    oA++;
+                const bool ang = r2 < rl2A;
+                if (oR < MAXR) {
+                    S.rowR[(size_t)oR * S.N + i] = ang && oA < MAXA ? j | ANG_BIT : j;
+                    S.r2a[(size_t)oR * S.N + i] = ang && oA < MAXA ? oA : NO_SLOT;
                 }
+                oA += ang;
                 oR++;
             }
         }
         if (act && lane == 0) {
             const bool over = nr > MAXR || na > MAXA;
-            S.cntR[i] = min(nr, MAXR);
-            S.cntFeR[i] = min(fR, MAXR);
-            S.cntA[i] = min(na, MAXA);
-            S.cntFeA[i] = min(fA, MAXA);
+            S.lenR[i] = min(nr, MAXR);
+            S.lenFeR[i] = min(fR, MAXR);
             if (over || (S.mag && i < S.N_fe && fR > MAXFE)) {
                 atomicOr(&S.flags[F_OVERFLOW], 1);
                 atomicOr(&S.rep[S.rid[i]].failed, 1);
@@ -362,38 +342,35 @@ __device__ inline int find_sorted(const int *nbr, int N, int row, int n, int key
     int lo = 0, hi = n;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        const int v = nbr[(size_t)mid * N + row];
+        const int v = nbr[(size_t)mid * N + row] & ~ANG_BIT;
         if (v < key) lo = mid + 1;
         else hi = mid;
     }
-    return (lo < n && nbr[(size_t)lo * N + row] == key) ? lo : -1;
+    return (lo < n && (nbr[(size_t)lo * N + row] & ~ANG_BIT) == key) ? lo : -1;
 }
 
-// reverse slots (where i sits in j's list), angular->radial slot map, and the
-// colouring check. A same-colour spin pair inside rc_R would be updated
+// reverse angular slots (where i sits in j's row) and the colouring check. A same-colour spin pair inside rc_R would be updated
 // concurrently by the sweep although coupled: the replica fails (bit 2). A
 // same-colour pair in the list shell (rc_R, rc_R + skin] is not coupled yet
 // and cannot come inside rc_R before the next rebuild, so the step stays
 // exact; the replica is paused at the end of the step for recolouring (bit 4).
-__global__ void k_rev(Sys S) {
+// Eight lanes per atom take its row's entries in turn: the searches are chains
+// of dependent scattered reads, so what counts is how many are in flight.
+__global__ void __launch_bounds__(256) k_rev(Sys S) {
     if (S.flags[F_REBUILD] == 0) return;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 7;
+    const int i = blockIdx.x * 32 + (threadIdx.x >> 3);
     if (i >= S.N) return;
-    const int na = S.cntA[i];
+    const int nr = S.lenR[i];
     int bad = 0;
-    // reverse radial slots: used by the spin couplings only (spin-carrying pairs)
-    const int nm = S.mag && i < S.N_fe ? min(S.cntFeR[i], MAXFE) : 0;
-    for (int s = 0; s < nm; s++) {
-        const int j = S.nbrR[(size_t)s * S.N + i];
-        const int r = find_sorted(S.nbrR, S.N, j, S.cntR[j], i);
-        bad |= r < 0;
-        S.revR[(size_t)s * S.N + i] = r < 0 ? 0 : r;
-    }
-    for (int s = 0; s < na; s++) {
-        const int j = S.nbrA[(size_t)s * S.N + i];
-        const int r = find_sorted(S.nbrA, S.N, j, S.cntA[j], i);
-        bad |= r < 0;
-        S.revA[(size_t)s * S.N + i] = r < 0 ? 0 : r;
+    for (int s = lane; s < nr; s += 8) {
+        const int v = S.rowR[(size_t)s * S.N + i];
+        if (!(v & ANG_BIT)) continue;
+        const int a = S.r2a[(size_t)s * S.N + i], j = v & ~ANG_BIT;
+        const int r = find_sorted(S.rowR, S.N, j, S.lenR[j], i);
+        const int b = r < 0 ? NO_SLOT : S.r2a[(size_t)r * S.N + j];
+        bad |= b == NO_SLOT;
+        S.revA[(size_t)a * S.N + i] = b == NO_SLOT ? 0 : b;
     }
     if (bad) {
         atomicOr(&S.flags[F_OVERFLOW], 2);
@@ -401,12 +378,12 @@ __global__ void k_rev(Sys S) {
     }
     if (S.colour && i < S.N_fe && S.colour[i] >= 0) {
         const int ci = S.colour[i];
-        const int nfe = S.cntFeR[i];
+        const int nfe = S.lenFeR[i];
         const RepDev &R = S.rep[S.rid[i]];
         const d4 pi = S.pos[i];
         int conflict = 0;
-        for (int s = 0; s < nfe; s++) {
-            const int j = S.nbrR[(size_t)s * S.N + i];
+        for (int s = lane; s < nfe; s += 8) {
+            const int j = S.rowR[(size_t)s * S.N + i] & ~ANG_BIT;
             if (S.colour[j] == ci) {
                 double dx, dy, dz;
                 min_image(R, pi, S.pos[j], dx, dy, dz);
@@ -442,7 +419,7 @@ void launch_rebuild(const Sys &S, double r_listR, double r_listA, hipStream_t st
     hipLaunchKernelGGL(k_build_cells, dim3(S.n_cells), dim3(BC), 0, st, S, r_listR * r_listR, r_listA * r_listA);
     hipLaunchKernelGGL(k_build, dim3(nblk(S.N, BLK)), dim3(BLK), 0, st, S, r_listR * r_listR,
                        r_listA * r_listA);
-    hipLaunchKernelGGL(k_rev, dim3(nblk(S.N, 256)), dim3(256), 0, st, S);
+    hipLaunchKernelGGL(k_rev, dim3(nblk(S.N, 32)), dim3(256), 0, st, S);
     hipLaunchKernelGGL(k_rebuild_done, dim3(1), dim3(64), 0, st, S);
 }
 
