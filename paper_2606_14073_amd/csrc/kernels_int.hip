@@ -155,6 +155,23 @@ __device__ inline double quad_bcast(double v) {
     return __hiloint2double(hi, lo);
 }
 
+template <int K>
+__device__ inline float quad_bcast(float v) {
+    constexpr int ctrl = K | (K << 2) | (K << 4) | (K << 6);
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ctrl, 0xF, 0xF, false));
+}
+
+// Value of the lane that differs in bit M of its number within sixteen, for a
+// butterfly sum over M = 1, 2, 4, 8 in turn (DPP; M = 4 and 8 read the mirrored
+// lane, which by then holds the same sum).
+template <int M>
+__device__ inline double row_partner(double v) {
+    constexpr int ctrl = M == 1 ? 0xB1 : M == 2 ? 0x4E : M == 4 ? 0x141 : 0x140;   // quad_perm, row_half_mirror, row_mirror
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
 // One coupling's contribution to the field on a spin: exchange J s_j, DMI
 // D s_j x r, anisotropic exchange K (s_j . r) r, subtracted from h, with
 // explicit fused multiply-adds and no other contraction.
@@ -168,11 +185,11 @@ __device__ inline void coupling_field(double J, double D, double K, double rx, d
     hz -= fma(J, sz, fma(D, fma(sx, ry, -(sy * rx)), ks * rz));
 }
 
-// One colour class: every spin takes an implicit-midpoint Rodrigues rotation
-// over tau = dt/2 in the field of its (other-colour) neighbours, its own
-// anisotropy/onsite terms at the midpoint, the Zeeman field and the noise.
-// L lanes share a spin (L = 4, 8 or 16): they split the neighbour gather
-// (couplings stored in colour-list order, so a wavefront reads contiguous
+// The sweep over a colour class: every spin takes an implicit-midpoint
+// Rodrigues rotation over tau = dt/2 in the field of its (other-colour)
+// neighbours, its own anisotropy/onsite terms at the midpoint, the Zeeman field
+// and the noise. L lanes share a spin (L = 4, 8 or 16): they split the neighbour
+// gather (couplings stored in colour-list order, so a wavefront reads contiguous
 // records), reduce, and then solve the midpoint equation together (each quad
 // of lanes evaluates the rotation at four points per Newton step); lane 0
 // stores the result.
@@ -181,87 +198,93 @@ __device__ inline void coupling_field(double J, double D, double K, double rx, d
 // over v (xor 1, 2, 4, 8) adds the sixteen partial sums. Lane l of L carries
 // the virtual lanes l + L k, k < 16 / L; the butterfly levels below L run
 // across lanes and the others inside the lane. A spin's result thus has the
-// same bits with any L, so each launch takes the L that suits the size of
-// its colour class (fewer, fuller waves for large classes, more workgroups
-// for small ones) and a replica still gives the same bits alone and in any
-// batch.
-// Latency is what bounds a colour class, so the loads are issued in two
-// waves: everything indexed by the colour-list position (atom, replica,
-// coupling count, self terms, the first 32 coupling slots, read whether or
-// not they are in use and masked afterwards), then the neighbours' spins, the
-// spin itself, its noise and the replica record.
+// same bits with any L, so each launch takes the L that suits the size of its
+// colour class (fewer, fuller waves for large classes, more workgroups for small
+// ones) and a replica still gives the same bits alone and in any batch.
+// The arithmetic is not contracted: the compiler would fuse multiplies and adds
+// differently in the instances (their code is scheduled apart), and their
+// results would then differ in the last bit; where a fused multiply-add is
+// wanted it is written out.
 constexpr int SWEEP_V = 16;              // virtual lanes of the field sum
 constexpr int SWEEP_WIDE_MIN = 8192;     // classes of at least this many spins take 8 lanes per spin
 constexpr int SWEEP_WIDER_MIN = 32768;   // and of at least this many 4
 
-// turns = 2 takes the colour twice in a row (the end of the ascending and the
-// start of the descending pass): the neighbour field is the same for both
-// rotations, the second starts from the first one's result.
-// The kernel's own arithmetic is not contracted: the compiler would fuse
-// multiplies and adds differently in the two lane layouts (their code is
-// scheduled apart), and their results would then differ in the last bit;
-// where a fused multiply-add is wanted it is written out.
+// what a visit needs that does not depend on the neighbours' spins: everything
+// indexed by the colour-list position p (atom, coupling count, self terms, the
+// first 32 coupling slots, read whether or not they are in use and masked
+// afterwards), then the atom's noise and spin
 template <typename real, int L>
-__global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, int count, int turns, int visit0) {
-#pragma clang fp contract(off)
-    constexpr int P = SWEEP_V / L;   // virtual lanes per lane
-    constexpr int R0 = 2 * P;        // coupling slots per lane loaded up front
-    const int lane = threadIdx.x & (L - 1);
-    const int t = blockIdx.x * (256 / L) + threadIdx.x / L;
-    if (t >= count) return;
-    const int p = base + t;
-    const size_t lf = S.N_fe;
-    // first wave of loads; up-front slot u = 2 k + w is slot lane + L k + 16 w
-    const int i = S.col_idx[p];
-    const int r = S.col_rid[p];
-    const int nc = W.cpl_n[p];
-    const real *o = W.selfc + (size_t)p * 8;
-    const double Axx = o[0], Ayy = o[1], Azz = o[2], Axy = o[3], Axz = o[4], Ayz = o[5], os = o[6];
-    int cj[R0];
-    double cv[R0][6];
+struct SweepSpin {
+    static constexpr int P = SWEEP_V / L;   // virtual lanes per lane
+    static constexpr int R0 = 2 * P;        // coupling slots per lane loaded up front: u = 2 k + w is lane + L k + 16 w
+    int p, i, nc, cj[R0];
+    real cv[R0][6], A[7];
+    d4 e, s4;
+    __device__ void load(const Sys &S, const Work<real> &W, int lane, int p_) {
+        p = p_;
+        const size_t lf = S.N_fe;
+        i = S.col_idx[p];
+        nc = W.cpl_n[p];
+        const real *o = W.selfc + (size_t)p * 8;
 #pragma unroll
-    for (int u = 0; u < R0; u++) {
-        const size_t q = (size_t)(lane + L * (u >> 1) + SWEEP_V * (u & 1)) * lf + p;
-        cj[u] = W.cpl_j[q];
-        const real *c = W.cpl + q * 6;
+        for (int x = 0; x < 7; x++) A[x] = o[x];
 #pragma unroll
-        for (int x = 0; x < 6; x++) cv[u][x] = c[x];
+        for (int u = 0; u < R0; u++) {
+            const size_t q = (size_t)(lane + L * (u >> 1) + SWEEP_V * (u & 1)) * lf + p;
+            cj[u] = W.cpl_j[q];
+            const real *c = W.cpl + q * 6;
+#pragma unroll
+            for (int x = 0; x < 6; x++) cv[u][x] = c[x];
+        }
     }
-    // second wave
-    const RepDev &R = S.rep[r];
-    const d4 e = S.eta[i];
-    const d4 s4 = S.spin[i];
+    __device__ void load_atom(const Sys &S) {
+        e = S.eta[i];
+        s4 = S.spin[i];
+    }
+};
+
+// the field of the neighbours on the spin, summed over its lanes
+template <typename real, int L>
+__device__ inline void sweep_field(const Sys &S, const Work<real> &W, const SweepSpin<real, L> &q, int lane, double &hx,
+                                   double &hy, double &hz) {
+#pragma clang fp contract(off)
+    constexpr int P = SweepSpin<real, L>::P, R0 = SweepSpin<real, L>::R0;
+    const size_t lf = S.N_fe;
     double px[P], py[P], pz[P];
 #pragma unroll
     for (int k = 0; k < P; k++) px[k] = py[k] = pz[k] = 0;
     d4 sj[R0];
 #pragma unroll
-    for (int u = 0; u < R0; u++) sj[u] = S.spin[lane + L * (u >> 1) + SWEEP_V * (u & 1) < nc ? cj[u] : i];
+    for (int u = 0; u < R0; u++)
+        sj[u] = S.spin[lane + L * (u >> 1) + SWEEP_V * (u & 1) < q.nc ? q.cj[u] : q.i];
 #pragma unroll
     for (int u = 0; u < R0; u++) {
         const int k = u >> 1;
-        if (lane + L * k + SWEEP_V * (u & 1) >= nc) continue;
-        coupling_field(cv[u][0], cv[u][1], cv[u][2], cv[u][3], cv[u][4], cv[u][5], sj[u].x, sj[u].y, sj[u].z, px[k],
-                       py[k], pz[k]);
+        if (lane + L * k + SWEEP_V * (u & 1) >= q.nc) continue;
+        coupling_field(q.cv[u][0], q.cv[u][1], q.cv[u][2], q.cv[u][3], q.cv[u][4], q.cv[u][5], sj[u].x, sj[u].y,
+                       sj[u].z, px[k], py[k], pz[k]);
     }
     // spins with more than 32 couplings
 #pragma unroll
     for (int k = 0; k < P; k++)
-        for (int s = lane + L * k + 2 * SWEEP_V; s < nc; s += SWEEP_V) {
-            const int j = W.cpl_j[(size_t)s * lf + p];
-            const real *c = W.cpl + ((size_t)s * lf + p) * 6;
+        for (int s = lane + L * k + 2 * SWEEP_V; s < q.nc; s += SWEEP_V) {
+            const int j = W.cpl_j[(size_t)s * lf + q.p];
+            const real *c = W.cpl + ((size_t)s * lf + q.p) * 6;
             const d4 v = S.spin[j];
             coupling_field(c[0], c[1], c[2], c[3], c[4], c[5], v.x, v.y, v.z, px[k], py[k], pz[k]);
         }
     // butterfly: levels 1 .. L/2 across the lanes, then L .. 8 inside them
+    static_for<4>([&](auto B) {
+        constexpr int m = 1 << decltype(B)::value;
+        if constexpr (m < L) {
 #pragma unroll
-    for (int m = 1; m < L; m <<= 1)
-#pragma unroll
-        for (int k = 0; k < P; k++) {
-            px[k] += __shfl_xor(px[k], m);
-            py[k] += __shfl_xor(py[k], m);
-            pz[k] += __shfl_xor(pz[k], m);
+            for (int k = 0; k < P; k++) {
+                px[k] += row_partner<m>(px[k]);
+                py[k] += row_partner<m>(py[k]);
+                pz[k] += row_partner<m>(pz[k]);
+            }
         }
+    });
 #pragma unroll
     for (int b = 1; b < P; b <<= 1)
 #pragma unroll
@@ -270,17 +293,50 @@ __global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, in
             py[k] += py[k + b];
             pz[k] += pz[k + b];
         }
-    double hx = px[0], hy = py[0], hz = pz[0];
-    if (!spin_pass_on(R)) return;
-    const double fr = ramp_frac(R), zs = R.mu_s * MUB;
-    hx += fma(zs, fma(R.B1[0] - R.B0[0], fr, R.B0[0]), e.x);
-    hy += fma(zs, fma(R.B1[1] - R.B0[1], fr, R.B0[1]), e.y);
-    hz += fma(zs, fma(R.B1[2] - R.B0[2], fr, R.B0[2]), e.z);
-    const double al = R.alpha, inv = 1.0 / fma(al, al, 1.0), tau = 0.5 * R.dt / HBAR;
-    const double tol = R.mid_tol;
-    const int cap = R.mid_cap;
+    hx = px[0];
+    hy = py[0];
+    hz = pz[0];
+}
+
+// the replica's constants of the spin step
+struct SweepConst {
+    double zs, B[3], al, inv, tau, tol, la2, lb4;
+    int cap;
+};
+__device__ inline SweepConst sweep_const(const RepDev &R) {
+    SweepConst c;
+    const double fr = ramp_frac(R);
+    c.zs = R.mu_s * MUB;
+#pragma unroll
+    for (int a = 0; a < 3; a++) c.B[a] = fma(R.B1[a] - R.B0[a], fr, R.B0[a]);
+    c.al = R.alpha;
+    c.inv = 1.0 / fma(R.alpha, R.alpha, 1.0);
+    c.tau = 0.5 * R.dt / HBAR;
+    c.tol = R.mid_tol;
+    c.cap = R.mid_cap;
+    c.la2 = 2.0 * R.landau_a;   // onsite moment-length term
+    c.lb4 = 4.0 * R.landau_b;
+    return c;
+}
+
+// The spin after its visit, from the neighbours' field h, and the number of its
+// rotations that stopped at the cap; every lane gets the same. turns = 2 takes
+// the colour twice in a row (the end of the ascending and the start of the
+// descending pass): the neighbour field is the same for both rotations, the
+// second starts from the first one's result.
+template <typename real, int L>
+__device__ inline int sweep_solve(const RepDev &R, const SweepConst &c, const SweepSpin<real, L> &q, uint32_t orig,
+                                  int lane, int turns, int visit0, double hx, double hy, double hz, double &yx, double &yy,
+                                  double &yz) {
+#pragma clang fp contract(off)
+    const double Axx = q.A[0], Ayy = q.A[1], Azz = q.A[2], Axy = q.A[3], Axz = q.A[4], Ayz = q.A[5], os = q.A[6];
+    const d4 e = q.e, s4 = q.s4;
+    hx += fma(c.zs, c.B[0], e.x);
+    hy += fma(c.zs, c.B[1], e.y);
+    hz += fma(c.zs, c.B[2], e.z);
+    const double al = c.al, inv = c.inv, tau = c.tau, tol = c.tol, la2 = c.la2, lb4 = c.lb4;
+    const int cap = c.cap;
     const double Dxx = Axx + os, Dyy = Ayy + os, Dzz = Azz + os;   // A_i + o_i I
-    const double la2 = 2.0 * R.landau_a, lb4 = 4.0 * R.landau_b;   // onsite moment-length term
     double sx = s4.x, sy = s4.y, sz = s4.z;
     double len = 1.0;    // length of the midpoint vector: 1, or |s| for spins of variable length
     // G(y): the spin rotated about the precession vector taken at the
@@ -322,6 +378,34 @@ __global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, in
         ny = fma(uy, uo, fma(fma(uz, sx, -(ux * sz)), sn, sy * cs));
         nz = fma(uz, uo, fma(fma(ux, sy, -(uy * sx)), sn, sz * cs));
     };
+    // the same in single precision, for a starting point only
+    const float fhx = (float)hx, fhy = (float)hy, fhz = (float)hz, fal = (float)al, finv = (float)inv, ftau = (float)tau;
+    const float gxx = (float)Dxx, gyy = (float)Dyy, gzz = (float)Dzz, gxy = (float)Axy, gxz = (float)Axz, gyz = (float)Ayz;
+    const float fla2 = (float)la2, flb4 = (float)lb4;
+    auto rotate_f = [&](float sx, float sy, float sz, float ln, float px, float py, float pz, float &nx, float &ny,
+                        float &nz) {
+        float mx = sx + px, my = sy + py, mz = sz + pz;
+        const float mn = __builtin_amdgcn_rsqf(fmaf(mz, mz, fmaf(my, my, mx * mx))) * ln;
+        mx *= mn;
+        my *= mn;
+        mz *= mn;
+        const float kl = fmaf(flb4, ln * ln, fla2);
+        const float h0 = fmaf(-kl, mx, fmaf(-2.0f, fmaf(gxz, mz, fmaf(gxy, my, gxx * mx)), fhx));
+        const float h1 = fmaf(-kl, my, fmaf(-2.0f, fmaf(gyz, mz, fmaf(gyy, my, gxy * mx)), fhy));
+        const float h2 = fmaf(-kl, mz, fmaf(-2.0f, fmaf(gzz, mz, fmaf(gyz, my, gxz * mx)), fhz));
+        const float wx = fmaf(fal, fmaf(my, h2, -(mz * h1)), h0) * finv;
+        const float wy = fmaf(fal, fmaf(mz, h0, -(mx * h2)), h1) * finv;
+        const float wz = fmaf(fal, fmaf(mx, h1, -(my * h0)), h2) * finv;
+        const float w2 = fmaxf(fmaf(wz, wz, fmaf(wy, wy, wx * wx)), 1.0e-30f);
+        const float iw = __builtin_amdgcn_rsqf(w2);
+        const float rev = w2 * iw * ftau * 0.15915494f;   // |w| tau in revolutions
+        const float sn = __builtin_amdgcn_sinf(rev), cs = __builtin_amdgcn_cosf(rev);
+        const float ux = wx * iw, uy = wy * iw, uz = wz * iw;
+        const float uo = fmaf(uz, sz, fmaf(uy, sy, ux * sx)) * (1.0f - cs);
+        nx = fmaf(ux, uo, fmaf(fmaf(uy, sz, -(uz * sy)), sn, sx * cs));
+        ny = fmaf(uy, uo, fmaf(fmaf(uz, sx, -(ux * sz)), sn, sy * cs));
+        nz = fmaf(uz, uo, fmaf(fmaf(ux, sy, -(uy * sx)), sn, sz * cs));
+    };
     // The midpoint equation y = G(y) is solved by Newton's method on
     // G(y) - y with a forward-difference Jacobian: the four lanes of each
     // quad evaluate G at y and at y + h e_x, y + h e_y, y + h e_z at once
@@ -329,10 +413,18 @@ __global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, in
     // quad broadcasts and take the same step. The iteration stops, as the
     // plain fixed-point one, when |G(y) - y| <= tol, and returns G(y): a
     // rotation of the spin, so its length is kept. The Jacobian's relative
-    // error (about 1e-8 from the step h = 2^-26) only slows the final
+    // error (about 1e-9 from the step h = 2^-23) only slows the final
     // convergence to linear with that ratio.
+    // The chain of dependent FP64 operations is what a visit costs (about 1,650
+    // cycles an iteration), so the first two iterations, which only have to come
+    // near, run in FP32 (step 2^-11): from about 1e-7 one FP64 iteration reaches
+    // the tolerance and the next one finds that it did, where from y = s it took
+    // three and that one. 512 atoms 5.75 -> 5.4 us per
+    // colour launch, 262,144 atoms 8.3 -> 7.6 (FP32-mixed 7.6 -> 7.2).
     const int sub = lane & 3;
-    constexpr double FD_H = 0x1p-26, FD_IH = 0x1p26;
+    constexpr double FD_H = 0x1p-23, FD_IH = 0x1p23;
+    constexpr float FF_H = 0x1p-11f, FF_IH = 0x1p11f;
+    constexpr int PRE = 2;   // FP32 iterations, counted as iterations
     // Spins of variable length with damping: the rotation sits between two
     // longitudinal half steps of the Langevin dynamics over dt/4 each,
     // x += (gamma t/hbar) h(x) + sqrt(2 gamma kB T t/hbar) xi, h the full
@@ -349,13 +441,15 @@ __global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, in
         const double f1 = hy - 2.0 * (Axy * x + Dyy * y + Ayz * z) - kl * y;
         const double f2 = hz - 2.0 * (Axz * x + Ayz * y + Dzz * z) - kl * z;
         double xi[3] = {0.0, 0.0, 0.0};
-        if (T > 0) gauss3(R.seed, (uint32_t)S.orig[i], (unsigned long long)R.step, stream, xi);
+        if (T > 0) gauss3(R.seed, orig, (unsigned long long)R.step, stream, xi);
         const double k = R.lsf_gamma * t / HBAR, sig = sqrt(2.0 * R.lsf_gamma * KB * T * t / HBAR);
         x += k * f0 + sig * xi[0];
         y += k * f1 + sig * xi[1];
         z += k * f2 + sig * xi[2];
     };
-    double yx = sx, yy = sy, yz = sz;
+    yx = sx;
+    yy = sy;
+    yz = sz;
     int ncapped = 0;
     for (int turn = 0; turn < turns; turn++) {
         if (turn) {
@@ -369,7 +463,42 @@ __global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, in
         yx = sx;
         yy = sy;
         yz = sz;
-        for (int it = 0; it < cap; it++) {
+        int it0 = 0;
+        if (cap > 2 * PRE) {
+            const float fx = (float)sx, fy = (float)sy, fz = (float)sz, ln = (float)len;
+            float zx = fx, zy = fy, zz = fz, first = 0, last = 0;
+#pragma unroll
+            for (int k = 0; k < PRE; k++) {
+                float nx, ny, nz;
+                rotate_f(fx, fy, fz, ln, zx + (sub == 1 ? FF_H : 0.0f), zy + (sub == 2 ? FF_H : 0.0f),
+                         zz + (sub == 3 ? FF_H : 0.0f), nx, ny, nz);
+                const float g0x = quad_bcast<0>(nx), g0y = quad_bcast<0>(ny), g0z = quad_bcast<0>(nz);
+                const float rx = g0x - zx, ry = g0y - zy, rz = g0z - zz;
+                last = fmaxf(fabsf(rx), fmaxf(fabsf(ry), fabsf(rz)));
+                if (k == 0) first = last;
+                const float a00 = 1.0f - (quad_bcast<1>(nx) - g0x) * FF_IH, a10 = -(quad_bcast<1>(ny) - g0y) * FF_IH,
+                            a20 = -(quad_bcast<1>(nz) - g0z) * FF_IH;
+                const float a01 = -(quad_bcast<2>(nx) - g0x) * FF_IH, a11 = 1.0f - (quad_bcast<2>(ny) - g0y) * FF_IH,
+                            a21 = -(quad_bcast<2>(nz) - g0z) * FF_IH;
+                const float a02 = -(quad_bcast<3>(nx) - g0x) * FF_IH, a12 = -(quad_bcast<3>(ny) - g0y) * FF_IH,
+                            a22 = 1.0f - (quad_bcast<3>(nz) - g0z) * FF_IH;
+                auto det2 = [](float a, float b, float c, float d) { return fmaf(a, b, -(c * d)); };
+                const float c00 = det2(a11, a22, a12, a21), c01 = det2(a12, a20, a10, a22),
+                            c02 = det2(a10, a21, a11, a20);
+                const float id = __builtin_amdgcn_rcpf(fmaf(a02, c02, fmaf(a01, c01, a00 * c00)));
+                zx = fmaf(fmaf(det2(a01, a12, a02, a11), rz, fmaf(det2(a02, a21, a01, a22), ry, c00 * rx)), id, zx);
+                zy = fmaf(fmaf(det2(a02, a10, a00, a12), rz, fmaf(det2(a00, a22, a02, a20), ry, c01 * rx)), id, zy);
+                zz = fmaf(fmaf(det2(a00, a11, a01, a10), rz, fmaf(det2(a01, a20, a00, a21), ry, c02 * rx)), id, zz);
+            }
+            // taken only where it converges (also false for NaN)
+            if (last < 0.01f && last <= 0.1f * first && fabsf(zx) + fabsf(zy) + fabsf(zz) < 1.0e4f) {
+                yx = zx;
+                yy = zy;
+                yz = zz;
+                it0 = PRE;
+            }
+        }
+        for (int it = it0; it < cap; it++) {
             double nx, ny, nz;
             rotate(yx + (sub == 1 ? FD_H : 0.0), yy + (sub == 2 ? FD_H : 0.0), yz + (sub == 3 ? FD_H : 0.0), nx, ny,
                    nz);
@@ -396,7 +525,8 @@ __global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, in
             const double c00 = det2(a11, a22, a12, a21), c01 = det2(a12, a20, a10, a22), c02 = det2(a10, a21, a11, a20);
             const double det = fma(a02, c02, fma(a01, c01, a00 * c00));
             if (fabs(det) > 0.25) {
-                const double id = 1.0 / det;
+                double id = __builtin_amdgcn_rcp(det);   // refined once: a step needs no more
+                id = fma(fma(-det, id, 1.0), id, id);
                 yx += fma(det2(a01, a12, a02, a11), rz, fma(det2(a02, a21, a01, a22), ry, c00 * rx)) * id;
                 yy += fma(det2(a02, a10, a00, a12), rz, fma(det2(a00, a22, a02, a20), ry, c01 * rx)) * id;
                 yz += fma(det2(a00, a11, a01, a10), rz, fma(det2(a01, a20, a00, a21), ry, c02 * rx)) * id;
@@ -408,9 +538,27 @@ __global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, in
         }
         if (lsf_damp) lsf_half(yx, yy, yz, 3u + 2u * visit);
     }
+    return ncapped;
+}
+
+// One colour class per launch. Latency is what bounds a class: list position ->
+// couplings -> neighbour spins -> midpoint solve -> store.
+template <typename real, int L>
+__global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, int count, int turns, int visit0) {
+    const int lane = threadIdx.x & (L - 1);
+    const int t = blockIdx.x * (256 / L) + threadIdx.x / L;
+    if (t >= count) return;
+    SweepSpin<real, L> q;
+    q.load(S, W, lane, base + t);
+    const int r = S.col_rid[base + t];
+    q.load_atom(S);
+    const RepDev &R = S.rep[r];
+    if (!spin_pass_on(R)) return;
+    double hx, hy, hz, yx, yy, yz;
+    sweep_field<real, L>(S, W, q, lane, hx, hy, hz);
+    const int ncapped = sweep_solve(R, sweep_const(R), q, (uint32_t)S.orig[q.i], lane, turns, visit0, hx, hy, hz, yx, yy, yz);
     if (lane == 0) {
-        d4 out = {yx, yy, yz, 0.0};
-        S.spin[i] = out;
+        S.spin[q.i] = d4{yx, yy, yz, 0.0};
         if (ncapped) atomicAdd(&S.rep[r].capped, ncapped);
     }
 }
