@@ -351,6 +351,8 @@ int sl_destroy(sl_sim *s);
  *   9 lattice half-steps, baths and reductions
  *  10 spin-pair coupling assembly
  *  11 backward (angular set), species 1
+ * Systems of at most 65,536 atoms run groups 0 and 3 (but for the coefficients)
+ * in the launches of groups 1 and 4, and group 11 in that of group 4.
  * mask: bit g enables group g (0 disables timing). */
 #define SL_NPROF 12
 int sl_profile_enable(sl_sim *s, unsigned mask);

@@ -68,6 +68,7 @@ struct RepDev {
     double lsf_gamma;               // damping of the longitudinal spin dynamics
     int lsf;                        // 1: spins of variable length (longitudinal Langevin dynamics)
     int capped;                     // rotations of this step stopped at mid_cap without meeting mid_tol
+    int wide;                       // 1: radial-set sums over WIDE_LANES lanes per atom (a small replica)
     int sc_passes;                  // sweep passes of the last spin step (self-consistent batches)
     double sc_last;                 // and the change of its last pass
 };

@@ -341,6 +341,8 @@ struct Engine {
         S.N = N;
         S.N_fe = N_fe;
         S.mag = M && M->structural ? 0 : 1;
+        S.wide = S.narrow = 0;
+        for (const Replica *r : reps) (r->dev.wide ? S.wide : S.narrow) = 1;
         S.n_rep = (int)reps.size();
         S.n_cells = n_cells;
         S.rid = rid;
@@ -1310,6 +1312,7 @@ static int make_replica(const sl_system_view *sys, const double *vel, const int3
     d.skin = skin;
     d.active = 1;
     d.step_end = LLONG_MAX;
+    d.wide = n <= WIDE_MAX_ATOMS;
     d.mass[0] = mass_of(0);
     d.mass[1] = mass_of(1);
     if (ip) {

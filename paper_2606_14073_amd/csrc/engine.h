@@ -6,6 +6,18 @@
 namespace nep {
 
 constexpr int MAXFE = 64;     // listed spin-carrying neighbours kept for the spin couplings
+// Replicas of at most this many atoms spread an atom's radial-set pairs over
+// WIDE_LANES lanes, larger ones keep a lane per atom. It goes by the replica's
+// own size: the two sum in different orders, and a replica's bits must not
+// depend on what shares the batch. A lane per atom is a chain of some 60 pairs
+// and leaves the chip idle (512 atoms: 39 to 79 us a kernel); eight lanes cost
+// a tenth more work in their sums. FP64 step, one against eight lanes: 512 atoms
+// 1.37 / 1.06 ms, 32,768 1.89 / 1.63, 64,000 2.30 / 2.20, 110,592 2.91 / 3.11;
+// FP32-mixed 1.28 / 0.99, 1.60 / 1.34, 1.89 / 1.71, 2.29 / 2.26; water of 41,472
+// atoms 0.59 / 0.50, of 98,304 0.99 / 1.05.
+constexpr int WIDE_LANES = 8;
+constexpr long long WIDE_MAX_ATOMS = 65536;
+
 constexpr int RCOEF = 4 * NB; // per-atom contracted radial-set coefficients
 constexpr int MCOEF = 3 * NB; // per-spin-carrier contracted magnetic pair coefficients
 
@@ -20,6 +32,7 @@ enum { F_REBUILD = 0, F_OVERFLOW = 1, F_COLOUR = 2, F_NONFINITE = 3, NFLAGS = 8 
 // Slot-major neighbour arrays are indexed [slot * N + atom].
 struct Sys {
     int N, N_fe, n_rep, n_cells;
+    int wide, narrow;      // some resident replica is wide; some is not
     int mag;               // 1: spin-aware model; 0: structural-only (no spin work, N_fe = species-0 count)
     const int *rid;        // [N]
     const int *orig;       // [N] index in the replica's caller order
@@ -96,6 +109,8 @@ enum { PASS_FULL = 0, PASS_SPIN = 1, PASS_SPIN_REUSE = 2 };
 // atom or (the spin step) of the spin carriers
 template <typename real>
 void launch_active(const Sys &S, int mode, hipStream_t st);
+// radial set of the replicas with a lane per atom; the angular set of all
+// replicas together with the radial set of the wide ones
 template <typename real>
 void launch_desc_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &W, const d4 *spin, int mode,
                         hipStream_t st);
@@ -106,9 +121,10 @@ template <typename real>
 void launch_mlp(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int mode, hipStream_t st);
 template <typename real>
 void launch_bwd_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &W, hipStream_t st);
+// the angular set of species 0 (spin carriers) or 1; where some replica is
+// wide, species 0 stands for both and for the wide replicas' radial set
 template <typename real>
-void launch_bwd_angular(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int species,
-                        hipStream_t st);   // one launch: species 0 (spin carriers) or 1
+void launch_bwd_angular(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int species, hipStream_t st);
 template <typename real>
 void launch_gather(const Sys &S, const Work<real> &W, hipStream_t st);
 template <typename real>

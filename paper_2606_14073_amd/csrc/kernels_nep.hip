@@ -23,9 +23,8 @@ namespace nep {
 
 namespace {
 
-// grid split: blocks [0, nbFe) take spin carriers, the rest the others
-__device__ inline int atom_of_block(const Sys &S, int per_block, int nbFe, int local, bool &fe) {
-    const int b = blockIdx.x;
+// grid split: blocks b in [0, nbFe) take spin carriers, the rest the others
+__device__ inline int atom_of_block(const Sys &S, int b, int per_block, int nbFe, int local, bool &fe) {
     if (b < nbFe) {
         fe = true;
         const int i = b * per_block + local;
@@ -39,6 +38,34 @@ __device__ inline int atom_of_block(const Sys &S, int per_block, int nbFe, int l
 // i, or -1 when its replica is not advancing (paused for a new colouring,
 // finished, or its step void): the force-field kernels leave such atoms alone
 __device__ inline int live(const Sys &S, int i) { return i >= 0 && S.rep[S.rid[i]].active ? i : -1; }
+// the same for the radial-set sums over L lanes per atom
+template <int L>
+__device__ inline int live_lanes(const Sys &S, int i) {
+    if (i < 0) return -1;
+    const RepDev &R = S.rep[S.rid[i]];
+    return R.active && (R.wide != 0) == (L > 1) ? i : -1;
+}
+
+// v summed over the L = 1 or 8 neighbouring lanes of an atom, every lane with
+// the result: xor 1, 2 and (the mirrored lane, whose quad holds the same sum) 4
+template <int CTRL>
+__device__ inline double dpp(double v) {
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false));
+}
+template <int CTRL>
+__device__ inline float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+template <int L, typename real>
+__device__ inline real lane_sum(real v) {
+    if constexpr (L > 1) {
+        v += dpp<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+        v += dpp<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+        v += dpp<0x141>(v);   // row_half_mirror
+    }
+    return v;
+}
 
 template <typename real>
 __device__ inline void load_spin(const d4 *sp, int j, real s[3]) {
@@ -95,14 +122,6 @@ __device__ inline real dotk(const real C[NB], const real f[NB]) {
 #pragma unroll
     for (int k = 0; k < NB; k++) s += C[k] * f[k];
     return s;
-}
-
-template <typename real>
-__device__ inline real xor_sum8(real v) {
-    v += __shfl_xor(v, 1);
-    v += __shfl_xor(v, 2);
-    v += __shfl_xor(v, 4);
-    return v;
 }
 
 // -------------------------------------------------------------------------
@@ -247,14 +266,16 @@ __global__ void __launch_bounds__(256) k_active(Sys S, int n) {
 }
 
 // -------------------------------------------------------------------------
-// forward: radial set (lane per atom)
+// forward: radial set, L lanes per atom: lane l takes the in-cutoff pairs of
+// rank l modulo L
 // -------------------------------------------------------------------------
 
-template <typename real>
-__global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restrict__ C, Work<real> W,
-                                                     const d4 *spin, int nbFe) {
+template <typename real, int L, int THREADS>
+__device__ __forceinline__ void desc_radial(const Sys &S, const real *__restrict__ C, const Work<real> &W, const d4 *spin,
+                                            int block, int nbFe) {
     bool fe;
-    const int i = live(S, atom_of_block(S, 256, nbFe, threadIdx.x, fe));
+    const int l = threadIdx.x % L;
+    const int i = live_lanes<L>(S, atom_of_block(S, block, THREADS / L, nbFe, threadIdx.x / L, fe));
     if (i < 0) return;
     const Img R = img_of(S.rep[S.rid[i]]);
     const d4 pi = S.pos[i];
@@ -273,15 +294,15 @@ __global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restri
 #pragma unroll
         for (int k = 0; k < NB; k++) FR[k] = FE[k] = FD[k] = FA[k] = FS[k] = 0;
         // neighbour index two slots ahead, position and spin one slot ahead
-        int j1 = 0 < nfe ? row[0] : 0;
-        int j2 = 1 < nfe ? row[ld] : j1;
+        int j1 = l < nfe ? row[(size_t)l * ld] : 0;
+        int j2 = l + L < nfe ? row[(size_t)(l + L) * ld] : j1;
         d4 p1 = S.pos[j1], v1 = spin[j1];
-        for (int s = 0; s < nfe; s++) {
+        for (int s = l; s < nfe; s += L) {
             const d4 pj = p1, vj = v1;
             j1 = j2;
             p1 = S.pos[j1];
             v1 = spin[j1];
-            if (s + 2 < nfe) j2 = row[(size_t)(s + 2) * ld];
+            if (s + 2 * L < nfe) j2 = row[(size_t)(s + 2 * L) * ld];
             real d[3];
             const real r2 = geom_p(R, pi, pj, d);
             real r, ir;
@@ -327,15 +348,14 @@ __global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restri
         // non-magnetic neighbours: only the radial and single-ion channels survive
 #pragma unroll
         for (int k = 0; k < NB; k++) FR[k] = FS[k] = 0;
-        int j1_ = nfe < cnt ? row[(size_t)nfe * ld] : 0;
-        int j2_ = nfe + 1 < cnt ? row[(size_t)(nfe + 1) * ld] : j1_;
+        int j1_ = nfe + l < cnt ? row[(size_t)(nfe + l) * ld] : 0;
+        int j2_ = nfe + l + L < cnt ? row[(size_t)(nfe + l + L) * ld] : j1_;
         d4 p1_ = S.pos[j1_];
-        for (int s = nfe; s < cnt; s++) {
-            const int j = j1_;
+        for (int s = nfe + l; s < cnt; s += L) {
             const d4 pj_ = p1_;
             j1_ = j2_;
             p1_ = S.pos[j1_];
-            if (s + 2 < cnt) j2_ = row[(size_t)(s + 2) * ld];
+            if (s + 2 * L < cnt) j2_ = row[(size_t)(s + 2 * L) * ld];
             real d[3];
             const real r2 = geom_p(R, pi, pj_, d);
             real r, ir;
@@ -361,22 +381,20 @@ __global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restri
             qR[n] += r_;
             qS[n] += s_;
         }
-        q[D_OS] = si[0] * si[0] + si[1] * si[1] + si[2] * si[2];
     } else {
         for (int part = 0; part < 2; part++) {
             real FR[NB];
 #pragma unroll
             for (int k = 0; k < NB; k++) FR[k] = 0;
-            const int b = part ? nfe : 0, e = part ? cnt : nfe;
+            const int b = (part ? nfe : 0) + l, e = part ? cnt : nfe;
             int j1_ = b < e ? row[(size_t)b * ld] : 0;
-            int j2_ = b + 1 < e ? row[(size_t)(b + 1) * ld] : j1_;
+            int j2_ = b + L < e ? row[(size_t)(b + L) * ld] : j1_;
             d4 p1_ = S.pos[j1_];
-            for (int s = b; s < e; s++) {
-                const int j = j1_;
+            for (int s = b; s < e; s += L) {
                 const d4 pj_ = p1_;
                 j1_ = j2_;
                 p1_ = S.pos[j1_];
-                if (s + 2 < e) j2_ = row[(size_t)(s + 2) * ld];
+                if (s + 2 * L < e) j2_ = row[(size_t)(s + 2 * L) * ld];
                 real d[3];
                 const real r2 = geom_p(R, pi, pj_, d);
                 real f[NB], r, ir;
@@ -394,8 +412,19 @@ __global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restri
                 qR[n] += r_;
             }
         }
-        q[D_OS] = 0;
     }
+#pragma unroll
+    for (int n = 0; n < NR; n++) {
+        qR[n] = lane_sum<L>(qR[n]);
+        if (fe && S.mag) {
+            qE[n] = lane_sum<L>(qE[n]);
+            qD[n] = lane_sum<L>(qD[n]);
+            qA[n] = lane_sum<L>(qA[n]);
+            qS[n] = lane_sum<L>(qS[n]);
+        }
+    }
+    if (l) return;
+    q[D_OS] = fe && S.mag ? si[0] * si[0] + si[1] * si[1] + si[2] * si[2] : real(0);
 #pragma unroll
     for (int n = 0; n < NR; n++) {
         q[D_R + n] = qR[n];
@@ -412,6 +441,12 @@ __global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restri
             q[D_SI + n] = qS[n];
         }
     }
+}
+
+template <typename real>
+__global__ void __launch_bounds__(256) k_desc_radial(Sys S, const real *__restrict__ C, Work<real> W,
+                                                     const d4 *spin, int nbFe) {
+    desc_radial<real, 1, 256>(S, C, W, spin, blockIdx.x, nbFe);
 }
 
 // -------------------------------------------------------------------------
@@ -495,13 +530,13 @@ __device__ inline real dotc(const real *c, const real f[NB]) {
 // assembly; PASS_SPIN_REUSE (same positions as the preceding PASS_SPIN)
 // takes A from it and only recomputes B and q^sa.
 template <typename real>
-__global__ void __launch_bounds__(64) k_desc_angular(Sys S, const real *__restrict__ C, Work<real> W,
-                                                     const d4 *spin, int nbFe, int mode) {
+__device__ __forceinline__ void desc_angular(const Sys &S, const real *__restrict__ C, const Work<real> &W,
+                                             const d4 *spin, int nbFe, int mode) {
     __shared__ real tile[ANG_ATOMS * ANG_TS];
     __shared__ int smax[2];
     const int lane = threadIdx.x & 7, slot = threadIdx.x >> 3;
     bool fe;
-    const int i = live(S, atom_of_block(S, ANG_ATOMS, nbFe, slot, fe));
+    const int i = live(S, atom_of_block(S, blockIdx.x, ANG_ATOMS, nbFe, slot, fe));
     const bool reuse = mode == PASS_SPIN_REUSE;
     if (threadIdx.x == 0) smax[0] = smax[1] = 0;
     __syncthreads();
@@ -669,6 +704,22 @@ __global__ void __launch_bounds__(64) k_desc_angular(Sys S, const real *__restri
 #pragma unroll
         for (int m = 0; m < NLM; m++) ab[NLM + m] = Bn[m];
     }
+}
+
+template <typename real>
+__global__ void __launch_bounds__(64) k_desc_angular(Sys S, const real *__restrict__ C, Work<real> W,
+                                                     const d4 *spin, int nbFe, int mode) {
+    desc_angular(S, C, W, spin, nbFe, mode);
+}
+
+// the same and the radial set of the wide replicas, in blocks of the same eight
+// atoms: the two do not depend on each other, and a small system is bound by
+// the length of its chain of launches
+template <typename real>
+__global__ void __launch_bounds__(64, 2) k_desc_both(Sys S, const real *__restrict__ C, Work<real> W, const d4 *spin,
+                                                  int nbFe, int nb, int mode) {
+    if ((int)blockIdx.x < nb) desc_angular(S, C, W, spin, nbFe, mode);
+    else desc_radial<real, WIDE_LANES, 64>(S, C, W, spin, blockIdx.x - nb, nbFe);
 }
 
 // -------------------------------------------------------------------------
@@ -991,10 +1042,12 @@ __device__ inline void short_range(const real *Z, int tau, real r, real ir, real
     dV = dv * s + v * ds;
 }
 
-template <typename real>
-__global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restrict__ C, Work<real> W, int nbFe) {
+template <typename real, int L, int THREADS>
+__device__ __forceinline__ void bwd_radial(const Sys &S, const real *__restrict__ C, const Work<real> &W, int block,
+                                           int nbFe) {
     bool fe;
-    const int i = live(S, atom_of_block(S, 256, nbFe, threadIdx.x, fe));
+    const int l = threadIdx.x % L;
+    const int i = live_lanes<L>(S, atom_of_block(S, block, THREADS / L, nbFe, threadIdx.x / L, fe));
     if (i < 0) return;
     const Img R = img_of(S.rep[S.rid[i]]);
     const d4 pi = S.pos[i];
@@ -1016,12 +1069,14 @@ __global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restric
         real si[3];
         load_spin(S.spin, i, si);
         const real os2 = real(2) * Fp[D_OS];
-        h[0] = os2 * si[0];
-        h[1] = os2 * si[1];
-        h[2] = os2 * si[2];
+        if (l == 0) {   // the atom's own terms, once
+            h[0] = os2 * si[0];
+            h[1] = os2 * si[1];
+            h[2] = os2 * si[2];
+        }
         // onsite moment-length term a|s|^2 + b|s|^4: its energy and dE/ds
         const RepDev &Rr = S.rep[S.rid[i]];
-        if (Rr.landau_a != 0.0 || Rr.landau_b != 0.0) {
+        if (l == 0 && (Rr.landau_a != 0.0 || Rr.landau_b != 0.0)) {
             const real la = (real)Rr.landau_a, lb = (real)Rr.landau_b;
             const real s2 = si[0] * si[0] + si[1] * si[1] + si[2] * si[2];
             const real kl = real(2) * la + real(4) * lb * s2;
@@ -1034,16 +1089,16 @@ __global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restric
             real CR[NB], CS[NB];
             contract((C + P_CR) + part * NR * NB, Fp + D_R, NR, CR);
             contract((C + P_CSI) + part * NR * NB, Fp + D_SI, NR, CS);
-            const int b = part ? nfe : 0, e = part ? cnt : nfe;
+            const int b = (part ? nfe : 0) + l, e = part ? cnt : nfe;
             int j1_ = b < e ? row[(size_t)b * ld] : 0;
-            int j2_ = b + 1 < e ? row[(size_t)(b + 1) * ld] : j1_;
+            int j2_ = b + L < e ? row[(size_t)(b + L) * ld] : j1_;
             d4 p1_ = S.pos[j1_];
-            for (int s = b; s < e; s++) {
+            for (int s = b; s < e; s += L) {
                 const int j = j1_;
                 const d4 pj_ = p1_;
                 j1_ = j2_;
                 p1_ = S.pos[j1_];
-                if (s + 2 < e) j2_ = row[(size_t)(s + 2) * ld];
+                if (s + 2 * L < e) j2_ = row[(size_t)(s + 2 * L) * ld];
                 real d[3];
                 const real r2 = geom_p(R, pi, pj_, d);
                 real r, ir;
@@ -1077,16 +1132,16 @@ __global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restric
         for (int part = 0; part < 2; part++) {
             real CR[NB];
             contract((C + P_CR) + ((fe ? 0 : 2) + part) * NR * NB, Fp + D_R, NR, CR);
-            const int b = part ? nfe : 0, e = part ? cnt : nfe;
+            const int b = (part ? nfe : 0) + l, e = part ? cnt : nfe;
             int j1_ = b < e ? row[(size_t)b * ld] : 0;
-            int j2_ = b + 1 < e ? row[(size_t)(b + 1) * ld] : j1_;
+            int j2_ = b + L < e ? row[(size_t)(b + L) * ld] : j1_;
             d4 p1_ = S.pos[j1_];
-            for (int s = b; s < e; s++) {
+            for (int s = b; s < e; s += L) {
                 const int j = j1_;
                 const d4 pj_ = p1_;
                 j1_ = j2_;
                 p1_ = S.pos[j1_];
-                if (s + 2 < e) j2_ = row[(size_t)(s + 2) * ld];
+                if (s + 2 * L < e) j2_ = row[(size_t)(s + 2 * L) * ld];
                 real d[3];
                 const real r2 = geom_p(R, pi, pj_, d);
                 real r, ir;
@@ -1109,8 +1164,20 @@ __global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restric
             }
         }
     }
+#pragma unroll
+    for (int x = 0; x < 3; x++) {
+        F[x] = lane_sum<L>(F[x]);
+        h[x] = lane_sum<L>(h[x]);
+    }
+    esr = lane_sum<L>(esr);
+    if (l) return;
     put_pair(W.ownR, (size_t)i, F, h);
     if (esr != real(0)) W.Ei[i] += esr;
+}
+
+template <typename real>
+__global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restrict__ C, Work<real> W, int nbFe) {
+    bwd_radial<real, 1, 256>(S, C, W, blockIdx.x, nbFe);
 }
 
 // Magnetic pair part of the radial-set backward pass: exchange, DMI and
@@ -1120,10 +1187,12 @@ __global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restric
 // for the anisotropic product), so a pair's force on i and field on s_i are
 // the formulas of e_ij with the summed coefficients C_i + C_j: no records.
 // Sums: F_i and dE/ds_i of these channels.
-template <typename real>
-__global__ void __launch_bounds__(256) k_bwd_mag(Sys S, const real *__restrict__ C, Work<real> W) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= S.N_fe || live(S, i) < 0) return;
+template <typename real, int L, int THREADS>
+__device__ __forceinline__ void bwd_mag(const Sys &S, const Work<real> &W, int block) {
+    const int l = threadIdx.x % L;
+    const int i0 = block * (THREADS / L) + threadIdx.x / L;
+    const int i = live_lanes<L>(S, i0 < S.N_fe ? i0 : -1);
+    if (i < 0) return;
     const Img R = img_of(S.rep[S.rid[i]]);
     const d4 pi = S.pos[i];
     const real rc = (real)RC_R;
@@ -1140,16 +1209,16 @@ __global__ void __launch_bounds__(256) k_bwd_mag(Sys S, const real *__restrict__
         for (int k = 0; k < 3 * NB; k++) Ci[k] = m[k];
     }
     // neighbour index two slots ahead, its position and spin one slot ahead
-    int j1_ = 0 < nfe ? row[0] : 0;
-    int j2_ = 1 < nfe ? row[ld] : j1_;
+    int j1_ = l < nfe ? row[(size_t)l * ld] : 0;
+    int j2_ = l + L < nfe ? row[(size_t)(l + L) * ld] : j1_;
     d4 p1_ = S.pos[j1_], v1_ = S.spin[j1_];
-    for (int s = 0; s < nfe; s++) {
+    for (int s = l; s < nfe; s += L) {
         const int j = j1_;
         const d4 pj_ = p1_, vj_ = v1_;
         j1_ = j2_;
         p1_ = S.pos[j1_];
         v1_ = S.spin[j1_];
-        if (s + 2 < nfe) j2_ = row[(size_t)(s + 2) * ld];
+        if (s + 2 * L < nfe) j2_ = row[(size_t)(s + 2 * L) * ld];
         real d[3];
         const real r2 = geom_p(R, pi, pj_, d);
         real r, ir;
@@ -1186,7 +1255,17 @@ __global__ void __launch_bounds__(256) k_bwd_mag(Sys S, const real *__restrict__
             h[x] += gE * sj[x] + gD * sjxr[x] + gA * b * rh[x];
         }
     }
-    put_pair(W.ownM, (size_t)i, F, h);
+#pragma unroll
+    for (int x = 0; x < 3; x++) {
+        F[x] = lane_sum<L>(F[x]);
+        h[x] = lane_sum<L>(h[x]);
+    }
+    if (l == 0) put_pair(W.ownM, (size_t)i, F, h);
+}
+
+template <typename real>
+__global__ void __launch_bounds__(256) k_bwd_mag(Sys S, Work<real> W) {
+    bwd_mag<real, 1, 256>(S, W, blockIdx.x);
 }
 
 // -------------------------------------------------------------------------
@@ -1217,14 +1296,12 @@ template <bool FE>
 constexpr int qstride() { return (FE ? 2 : 1) * NA * NLM + 1; }
 
 template <typename real, bool FE>
-__global__ void __launch_bounds__(64) k_bwd_angular(Sys S, const real *__restrict__ C, Work<real> W, int first,
-                                                    int last) {
+__device__ __forceinline__ void bwd_angular(const Sys &S, const real *__restrict__ C, const Work<real> &W, int first,
+                                            int last, int block, real *sQ, double *sAt) {
     constexpr int QSTRIDE = qstride<FE>();
-    __shared__ real sQ[ANG_ATOMS * QSTRIDE];
-    __shared__ double sAt[ANG_ATOMS * AT_W];
     const int tid = threadIdx.x, lane = tid & 7, slot = tid >> 3;
     const bool fe = first < S.N_fe;    // species 0: the pair types tau = 0, 1
-    const int i0 = first + blockIdx.x * ANG_ATOMS;
+    const int i0 = first + block * ANG_ATOMS;
     const int i = live(S, i0 + slot < last ? i0 + slot : -1);
     int cnt = 0, nfe = 0;
     if (i >= 0) {
@@ -1385,10 +1462,33 @@ __global__ void __launch_bounds__(64) k_bwd_angular(Sys S, const real *__restric
     // own-side sums over the atom's eight lanes (fixed xor tree)
 #pragma unroll
     for (int x = 0; x < 3; x++) {
-        Fo[x] = xor_sum8(Fo[x]);
-        ho[x] = xor_sum8(ho[x]);
+        Fo[x] = lane_sum<8>(Fo[x]);
+        ho[x] = lane_sum<8>(ho[x]);
     }
     if (lane == 0 && i >= 0) put_pair(W.ownA, (size_t)i, Fo, ho);
+}
+
+template <typename real, bool FE>
+__global__ void __launch_bounds__(64) k_bwd_angular(Sys S, const real *__restrict__ C, Work<real> W, int first,
+                                                    int last) {
+    __shared__ real sQ[ANG_ATOMS * qstride<FE>()];
+    __shared__ double sAt[ANG_ATOMS * AT_W];
+    bwd_angular<real, FE>(S, C, W, first, last, blockIdx.x, sQ, sAt);
+}
+
+// The whole backward pass of a batch with wide replicas: the angular set of
+// both species and, of the wide replicas, the radial set and the magnetic pairs,
+// which do not depend on each other, in blocks of eight atoms (see k_desc_both).
+template <typename real, bool MAG>
+__global__ void __launch_bounds__(64, 2) k_bwd_both(Sys S, const real *__restrict__ C, Work<real> W, int nbFe, int nb) {
+    __shared__ real sQ[ANG_ATOMS * qstride<MAG>()];
+    __shared__ double sAt[ANG_ATOMS * AT_W];
+    int b = blockIdx.x;
+    if (b < nbFe) return bwd_angular<real, MAG>(S, C, W, 0, S.N_fe, b, sQ, sAt);
+    if (b < nb) return bwd_angular<real, false>(S, C, W, S.N_fe, S.N, b - nbFe, sQ, sAt);
+    b -= nb;
+    if (b < nb) return bwd_radial<real, WIDE_LANES, 64>(S, C, W, b, nbFe);
+    if constexpr (MAG) bwd_mag<real, WIDE_LANES, 64>(S, W, b - nb);
 }
 
 // -------------------------------------------------------------------------
@@ -1422,8 +1522,8 @@ __global__ void __launch_bounds__(256) k_gather(Sys S, Work<real> W) {
     }
 #pragma unroll
     for (int x = 0; x < 3; x++) {
-        F[x] = xor_sum8(F[x]);
-        h[x] = xor_sum8(h[x]);
+        F[x] = lane_sum<8>(F[x]);
+        h[x] = lane_sum<8>(h[x]);
     }
     if (lane >= 3) return;   // lanes 0-2 finish one component each
     real Fx = lane == 0 ? F[0] : lane == 1 ? F[1] : F[2], hx = lane == 0 ? h[0] : lane == 1 ? h[1] : h[2];
@@ -1530,10 +1630,12 @@ __global__ void __launch_bounds__(64) k_assemble_angular(Sys S, const real *__re
 // lanes depends on the positions alone and not on which farther atoms the
 // Verlet list happens to hold. The same pass sums the single-ion tensor
 // A_i = sum_j g^si(r_ij) rhat rhat^T over all neighbours.
-template <typename real>
+template <typename real, int L>
 __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__restrict__ C, Work<real> W) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= S.N_fe || live(S, i) < 0) return;
+    const int l = threadIdx.x % L;
+    const int i0 = blockIdx.x * (256 / L) + threadIdx.x / L;
+    const int i = live_lanes<L>(S, i0 < S.N_fe ? i0 : -1);
+    if (i < 0) return;
     const Img R = img_of(S.rep[S.rid[i]]);
     const d4 pi = S.pos[i];
     const real rc = (real)RC_R, rc2 = rc * rc, rca = (real)RC_A, rca2 = rca * rca;   // as the angular pass
@@ -1553,15 +1655,15 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
         real CS[NB];
         contract((C + P_CSI), Fp + D_SI, NR, CS);
         // neighbour index two slots ahead, its position one slot ahead
-        int j1 = 0 < nfe ? row[0] : 0;
-        int j2 = 1 < nfe ? row[ld] : j1;
+        int j1 = l < nfe ? row[(size_t)l * ld] : 0;
+        int j2 = l + L < nfe ? row[(size_t)(l + L) * ld] : j1;
         d4 p1 = S.pos[j1];
-        for (int s = 0; s < nfe; s++) {
+        for (int s = l; s < nfe; s += L) {
             const int j = j1;
             const d4 pj = p1;
             j1 = j2;
             p1 = S.pos[j1];
-            if (s + 2 < nfe) j2 = row[(size_t)(s + 2) * ld];
+            if (s + 2 * L < nfe) j2 = row[(size_t)(s + 2 * L) * ld];
             real d[3];
             const real r2 = geom_p(R, pi, pj, d);
             real r, ir;
@@ -1601,14 +1703,15 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
     {
         real CS[NB];
         contract((C + P_CSI) + 1 * NR * NB, Fp + D_SI, NR, CS);
-        int j1 = nfe_all < cnt ? row[(size_t)nfe_all * ld] : 0;
-        int j2 = nfe_all + 1 < cnt ? row[(size_t)(nfe_all + 1) * ld] : j1;
+        const int b = nfe_all + l;
+        int j1 = b < cnt ? row[(size_t)b * ld] : 0;
+        int j2 = b + L < cnt ? row[(size_t)(b + L) * ld] : j1;
         d4 p1 = S.pos[j1];
-        for (int s = nfe_all; s < cnt; s++) {
+        for (int s = b; s < cnt; s += L) {
             const d4 pj = p1;
             j1 = j2;
             p1 = S.pos[j1];
-            if (s + 2 < cnt) j2 = row[(size_t)(s + 2) * ld];
+            if (s + 2 * L < cnt) j2 = row[(size_t)(s + 2 * L) * ld];
             real d[3];
             const real r2 = geom_p(R, pi, pj, d);
             real r, ir;
@@ -1625,6 +1728,13 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
             Ayz += g * rh[1] * rh[2];
         }
     }
+    Axx = lane_sum<L>(Axx);
+    Ayy = lane_sum<L>(Ayy);
+    Azz = lane_sum<L>(Azz);
+    Axy = lane_sum<L>(Axy);
+    Axz = lane_sum<L>(Axz);
+    Ayz = lane_sum<L>(Ayz);
+    if (l) return;
     real *o = W.selfc + (size_t)p * 8;
     o[0] = Axx;
     o[1] = Ayy;
@@ -1656,7 +1766,7 @@ void launch_active(const Sys &S, int mode, hipStream_t st) {
 template <typename real>
 void launch_desc_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &W, const d4 *spin, int mode,
                         hipStream_t st) {
-    if (S.N == 0) return;
+    if (S.N == 0 || !S.narrow) return;
     NEP_SPLIT(256)
     const int nb = mode == PASS_FULL ? nb_fe + nb_ge : nb_fe;
     if (nb) hipLaunchKernelGGL(k_desc_radial<real>, dim3(nb), dim3(256), 0, st, S, M.cR, W, spin, nb_fe);
@@ -1668,7 +1778,10 @@ void launch_desc_angular(const Sys &S, const ModelDev<real> &M, const Work<real>
     if (S.N == 0) return;
     NEP_SPLIT(ANG_ATOMS)
     const int nb = mode == PASS_FULL ? nb_fe + nb_ge : nb_fe;
-    if (nb)
+    if (!nb) return;
+    if (S.wide)
+        hipLaunchKernelGGL(k_desc_both<real>, dim3(2 * nb), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, spin, nb_fe, nb, mode);
+    else
         hipLaunchKernelGGL(k_desc_angular<real>, dim3(nb), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, spin, nb_fe, mode);
 }
 
@@ -1687,14 +1800,26 @@ void launch_bwd_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &
     if (S.N == 0) return;
     NEP_SPLIT(256)
     hipLaunchKernelGGL(k_radial_coef<real>, dim3(nblk(S.N, 256)), dim3(256), 0, st, S, M.cR, W);
+    if (!S.narrow) return;
     hipLaunchKernelGGL(k_bwd_radial<real>, dim3(nb_fe + nb_ge), dim3(256), 0, st, S, M.cR, W, nb_fe);
-    if (nb_fe && S.mag) hipLaunchKernelGGL(k_bwd_mag<real>, dim3(nb_fe), dim3(256), 0, st, S, M.cR, W);
+    if (nb_fe && S.mag) hipLaunchKernelGGL(k_bwd_mag<real>, dim3(nb_fe), dim3(256), 0, st, S, W);
 }
 
 template <typename real>
 void launch_bwd_angular(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int species, hipStream_t st) {
     if (S.N == 0) return;
     NEP_SPLIT(ANG_ATOMS)
+    if (S.wide) {
+        if (species) return;
+        const int nb = nb_fe + nb_ge;
+        if (S.mag)
+            hipLaunchKernelGGL((k_bwd_both<real, true>), dim3(2 * nb + nb_fe), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W,
+                               nb_fe, nb);
+        else
+            hipLaunchKernelGGL((k_bwd_both<real, false>), dim3(2 * nb), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, nb_fe,
+                               nb);
+        return;
+    }
     if (species == 0 && nb_fe) {
         if (S.mag)
             hipLaunchKernelGGL((k_bwd_angular<real, true>), dim3(nb_fe), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, 0,
@@ -1724,7 +1849,11 @@ void launch_assemble_coef(const Sys &S, const ModelDev<real> &M, const Work<real
 template <typename real>
 void launch_assemble_pairs(const Sys &S, const ModelDev<real> &M, const Work<real> &W, hipStream_t st) {
     if (S.N_fe == 0) return;
-    hipLaunchKernelGGL(k_assemble_pairs<real>, dim3(nblk(S.N_fe, 256)), dim3(256), 0, st, S, M.cR, W);
+    if (S.narrow)
+        hipLaunchKernelGGL((k_assemble_pairs<real, 1>), dim3(nblk(S.N_fe, 256)), dim3(256), 0, st, S, M.cR, W);
+    if (S.wide)
+        hipLaunchKernelGGL((k_assemble_pairs<real, WIDE_LANES>), dim3(nblk(S.N_fe, 256 / WIDE_LANES)), dim3(256), 0, st,
+                           S, M.cR, W);
 }
 
 #define NEP_INST(real)                                                                                           \
