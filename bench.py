@@ -42,7 +42,7 @@ from paper_2606_14073_amd import workload as W  # noqa: E402
 # MI355X published peaks
 PEAK = {"fp64": 78.6, "fp32": 157.3, "hbm_gbs": 8000.0}
 KERNEL_NAME = {"desc_radial": "k_desc_radial<{r}>", "desc_angular": "k_desc_angular<{r}>",
-               "readout": "k_mlp<{r},104>", "bwd_radial": "k_bwd_radial<{r}>",
+               "readout": "k_mlp<{r},104,false>", "bwd_radial": "k_bwd_radial<{r}>",
                "bwd_angular": "k_bwd_angular<{r},true>", "bwd_angular_1": "k_bwd_angular<{r},false>",
                "gather": "k_gather<{r}>", "couplings": "k_assemble_angular<{r}>", "pairs": "k_assemble_pairs<{r}>",
                "sweep": "k_sweep<{r}>", "nlist": "k_build_cells", "integrate": "k_kick"}

@@ -140,10 +140,45 @@ __device__ inline double dexp<double>(double x) { return exp(x); }
 template <>
 __device__ inline float dexp<float>(float x) { return expf(x); }
 
+// tanh x = t / (t + 2) with t = exp(2|x|) - 1 and the sign of x. t comes from
+// 2|x| = k ln 2 + r, |r| <= ln 2 / 2, as 2^k (exp(r) - 1) + (2^k - 1), exp(r) - 1
+// being its Taylor series (coefficients 1/n!, through r^13: truncation below
+// 2e-17 of it), so small arguments keep their relative accuracy (3 ulp). Beyond
+// 2|x| = 44 the result is 1 to rounding; NaN stays NaN. Straight-line, some 35
+// operations against the library's 150: the read-out takes 64 per atom, and
+// they cost as much FP64 issue as its matrix products. FP32, where the read-out
+// did not gain from the same, uses the library's.
 template <typename real>
 __device__ inline real dtanh(real x);
 template <>
-__device__ inline double dtanh<double>(double x) { return tanh(x); }
+__device__ inline double dtanh<double>(double x) {
+    double y = 2.0 * fabs(x);
+    y = y > 44.0 ? 44.0 : y;
+    const double k = rint(y * 1.4426950408889634074);
+    double r = fma(-k, 0x1.62e42fefap-1, y);     // ln 2, its first 33 bits: k times them is exact
+    r = fma(-k, 0x1.cf79abc9e3b3ap-40, r);       // and the rest
+    double p = 1.0 / 6227020800.0;               // 1/13!
+    p = fma(p, r, 1.0 / 479001600.0);
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p * r, r, r);
+    const double s = __hiloint2double(((int)k + 1023) << 20, 0);   // 2^k, 0 <= k <= 63
+    const double t = fma(s, p, s - 1.0), d = t + 2.0;
+    double c = __builtin_amdgcn_rcp(d);
+    c = fma(fma(-d, c, 1.0), c, c);
+    c = fma(fma(-d, c, 1.0), c, c);
+    double q = t * c;
+    q = fma(fma(-d, q, t), c, q);
+    return copysign(q, x);
+}
 template <>
 __device__ inline float dtanh<float>(float x) { return tanhf(x); }
 

@@ -731,6 +731,11 @@ __global__ void __launch_bounds__(64, 2) k_desc_both(Sys S, const real *__restri
 // A[i][k] in lane i + 16k, B[k][j] in lane j + 16k. Accumulator element r of
 // lane l holds column l % 16 and row 4 (l / 16) + r for the FP32
 // instruction, row (l / 16) + 4 r for the FP64 one (checked on gfx950).
+// Both products run transposed, Z^T = W0 Q^T (hidden x atoms) and Fp^T = W0^T
+// G^T: a lane's accumulators of the first are then, element for element, the B
+// operands it supplies to the second, whose contraction over the hidden units
+// is taken in the order that makes it so (k-step 4 mt + r is hidden unit
+// 16 mt + row(kq, r) in lane quarter kq). No transposition, no LDS tile.
 // -------------------------------------------------------------------------
 
 template <typename real>
@@ -750,10 +755,9 @@ struct MF<float> {
 
 constexpr int MLP_WAVES = 8;           // 8 wavefronts x 16 atoms per workgroup
 constexpr int MLP_ATOMS = 16 * MLP_WAVES;
-// LDS row strides of W0^T and of the per-wave hidden tile. The MFMA operand
-// reads walk 16 rows (lanes i16) and 4 columns (lanes kq); a stride of 2
-// dwords mod 64 for 8-byte and 4 dwords mod 64 for 4-byte elements puts those
-// 64 reads on distinct banks.
+// LDS row stride of W0^T. The operand reads walk 16 rows (lanes i16) and 4
+// columns (lanes kq); a stride of 2 dwords mod 64 for 8-byte elements puts those
+// reads on distinct banks, and of 4 dwords for the 16-byte reads of FP32.
 template <typename real>
 struct MlpLds;
 template <>
@@ -766,154 +770,147 @@ struct MlpLds<float> {
 };
 
 // KD: descriptor entries the read-out contracts over (104 for the spin-aware
-// model, 40 for the structural-only one, whose 37 entries lead each row)
-template <typename real, int KD>
+// model, 40 for the structural-only one, whose 37 entries lead each row).
+// SPIN: a spin-step pass, which needs neither E_i nor the gradient of the
+// structural entries: the tiles before the one that holds D_OS are left out.
+// What bounds it: FP64 shares its units between the matrix and the vector
+// instructions, and the library's tanh took as many cycles as the products; FP32
+// waited on scattered 4-byte reads and stores and on the LDS transposition of the
+// hidden tile. 2,097,152 atoms FP64, full pass 1.9 -> 1.43 ms, spin pass 0.95 ->
+// 0.61 (the products alone at the measured 71.8 TFLOP/s: 0.81 and 0.34);
+// 1,048,576 atoms FP32 0.60 -> 0.34 and 0.30 -> 0.17.
+template <typename real, int KD, bool SPIN>
 __global__ void __launch_bounds__(512) k_mlp(Sys S, ModelDev<real> M, Work<real> W, int nbFe) {
     typedef typename MF<real>::acc_t acc_t;
-    constexpr int WLD = MlpLds<real>::LD, GLD = MlpLds<real>::LD;
+    constexpr int WLD = MlpLds<real>::LD;
     constexpr bool f64 = sizeof(real) == 8;
     constexpr int KDT = (KD + 15) / 16 * 16, NT = KDT / 16;
-    __shared__ real sW[KDT * WLD];
-    __shared__ real sG[f64 ? 1 : MLP_WAVES * 16 * GLD];
+    constexpr int T0 = SPIN ? D_OS / 16 : 0;   // first gradient tile
+    __shared__ __align__(16) real sW[KDT * WLD];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const bool fe = (int)blockIdx.x < nbFe;
     const int t = fe ? 0 : 1;
     const int end = fe ? S.N_fe : S.N;
     const int a0 = (fe ? blockIdx.x * MLP_ATOMS : S.N_fe + (blockIdx.x - nbFe) * MLP_ATOMS) + wave * 16;
     const real *W0 = M.W0 + (size_t)t * DP * NH;
-    for (int x = threadIdx.x; x < KDT * NH; x += blockDim.x) {
-        const int d = x / NH, h = x - d * NH;
-        sW[d * WLD + h] = d < KD ? W0[d * NH + h] : real(0);
+    {
+        // all of the thread's values in flight at once
+        constexpr int SV = KDT * NH / (64 * MLP_WAVES);
+        static_assert(SV * 64 * MLP_WAVES == KDT * NH, "W0 is staged in whole rounds");
+        real w[SV];
+#pragma unroll
+        for (int v = 0; v < SV; v++) {
+            const int x = v * 64 * MLP_WAVES + threadIdx.x;
+            w[v] = x < KD * NH ? W0[x] : real(0);
+        }
+#pragma unroll
+        for (int v = 0; v < SV; v++) {
+            const int x = v * 64 * MLP_WAVES + threadIdx.x;
+            sW[(x / NH) * WLD + x % NH] = w[v];
+        }
     }
     __syncthreads();
     const int i16 = lane & 15, kq = lane >> 4;
     const int arow = a0 + i16;
     const bool rv = arow < end && live(S, arow) >= 0;
     const real *qrow = W.q + (size_t)(rv ? arow : 0) * DP;
+    // Z^T = W0 Q^T + b0. FP32 takes sixteen descriptor entries as four k-steps
+    // of four consecutive ones per lane quarter (one 16-byte load), the last
+    // eight as two of two.
+    auto entry = [&](int ks) {
+        if constexpr (f64) return ks * 4 + kq;
+        else return ks < KD / 16 * 4 ? (ks >> 2) * 16 + 4 * kq + (ks & 3) : KD / 16 * 16 + 2 * kq + (ks & 1);
+    };
+    real qa[KD / 4];
     if constexpr (f64) {
-        // Transposed form: Z^T = W0 Q^T + b0 (hidden x atoms). With the FP64
-        // accumulator layout, element r of tile mt in lane l is Z^T[16 mt +
-        // l/16 + 4 r][l % 16], which is exactly the B operand lane l supplies
-        // for k-step ks = 4 mt + r of Fp^T = W0^T G^T: no transposition.
-        real qa[KD / 4];
 #pragma unroll
         for (int ks = 0; ks < KD / 4; ks++) qa[ks] = rv ? qrow[ks * 4 + kq] : real(0);
-        acc_t z[4];
+    } else {
+        static_assert(KD % 16 == 8, "two k-steps after the sixteens");
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-            for (int r = 0; r < 4; r++) z[mt][r] = M.b0[t * NH + 16 * mt + kq + 4 * r];
-#pragma unroll
-        for (int ks = 0; ks < KD / 4; ks++) {
-#pragma unroll
-            for (int mt = 0; mt < 4; mt++)
-                z[mt] = MF<real>::mma(sW[(ks * 4 + kq) * WLD + mt * 16 + i16], qa[ks], z[mt]);
+        for (int g = 0; g < KD / 16; g++) {
+            const float4 v = rv ? *reinterpret_cast<const float4 *>(qrow + 16 * g + 4 * kq) : make_float4(0, 0, 0, 0);
+            qa[4 * g] = v.x;
+            qa[4 * g + 1] = v.y;
+            qa[4 * g + 2] = v.z;
+            qa[4 * g + 3] = v.w;
         }
-        real e = 0;
-        acc_t g[4];
+        const float2 v = rv ? *reinterpret_cast<const float2 *>(qrow + KD / 16 * 16 + 2 * kq) : make_float2(0, 0);
+        qa[KD / 4 - 2] = v.x;
+        qa[KD / 4 - 1] = v.y;
+    }
+    acc_t z[4];
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++)
+    for (int mt = 0; mt < 4; mt++)
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int hh = 16 * mt + kq + 4 * r;
-                const real w = M.w1[t * NH + hh];
-                const real a = dtanh<real>(z[mt][r]);
-                e += w * a;
-                g[mt][r] = w * (real(1) - a * a);
-            }
+        for (int r = 0; r < 4; r++) z[mt][r] = M.b0[t * NH + 16 * mt + MF<real>::row(kq, r)];
+#pragma unroll
+    for (int ks = 0; ks < KD / 4; ks++) {
+#pragma unroll
+        for (int mt = 0; mt < 4; mt++) z[mt] = MF<real>::mma(sW[entry(ks) * WLD + mt * 16 + i16], qa[ks], z[mt]);
+    }
+    // activation, energy and the hidden-layer gradient
+    real e = 0;
+    acc_t g[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const real w = M.w1[t * NH + 16 * mt + MF<real>::row(kq, r)];
+            const real a = dtanh<real>(z[mt][r]);
+            e += w * a;
+            g[mt][r] = w * (real(1) - a * a);
+        }
+    if (!SPIN) {
         e += __shfl_xor(e, 16);
         e += __shfl_xor(e, 32);
         if (kq == 0 && rv) W.Ei[arow] = M.b1[t] + e;
-        // Fp^T = W0^T G^T: A = W0^T tile from LDS, B = this lane's g; the
-        // descriptor tiles in passes of at most four to bound the registers
-        real *fp = W.Fp + (size_t)(rv ? arow : 0) * DP;
+    }
+    // Fp^T = W0^T G^T: A = W0^T tile from LDS, B = this lane's g; the
+    // descriptor tiles in passes of at most four to bound the registers
+    real *fp = W.Fp + (size_t)(rv ? arow : 0) * DP;
+    constexpr int H0 = 4;
 #pragma unroll
-        for (int half = 0; half < 2; half++) {
-            constexpr int H0 = 4;
-            const int d0 = half ? H0 : 0, nd = half ? NT - H0 : (NT < H0 ? NT : H0);
-            if (nd <= 0) continue;
-            acc_t f[H0];
+    for (int d0 = T0; d0 < NT; d0 += H0) {
+        acc_t f[H0];
 #pragma unroll
-            for (int x = 0; x < H0; x++) f[x] = acc_t{0, 0, 0, 0};
+        for (int x = 0; x < H0; x++) f[x] = acc_t{0, 0, 0, 0};
 #pragma unroll
-            for (int ks = 0; ks < NH / 4; ks++) {
+        for (int mt = 0; mt < 4; mt++) {
+            if constexpr (f64) {
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+#pragma unroll
+                    for (int x = 0; x < H0; x++)
+                        if (d0 + x < NT)
+                            f[x] = MF<real>::mma(sW[((d0 + x) * 16 + i16) * WLD + 16 * mt + 4 * r + kq], g[mt][r], f[x]);
+            } else {
 #pragma unroll
                 for (int x = 0; x < H0; x++)
-                    if (x < nd)
-                        f[x] = MF<real>::mma(sW[((d0 + x) * 16 + i16) * WLD + ks * 4 + kq], g[ks >> 2][ks & 3], f[x]);
-            }
-            if (rv) {
-#pragma unroll
-                for (int x = 0; x < H0; x++)
-#pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        const int d = (d0 + x) * 16 + kq + 4 * r;
-                        if (x < nd && d < KD) fp[d] = f[x][r];
+                    if (d0 + x < NT) {
+                        const float4 w =
+                            *reinterpret_cast<const float4 *>(&sW[((d0 + x) * 16 + i16) * WLD + 16 * mt + 4 * kq]);
+                        f[x] = MF<real>::mma(w.x, g[mt][0], f[x]);
+                        f[x] = MF<real>::mma(w.y, g[mt][1], f[x]);
+                        f[x] = MF<real>::mma(w.z, g[mt][2], f[x]);
+                        f[x] = MF<real>::mma(w.w, g[mt][3], f[x]);
                     }
             }
         }
-        return;
-    }
-    acc_t acc[4];
+        if (!rv) continue;
 #pragma unroll
-    for (int jt = 0; jt < 4; jt++) {
-        const real b0 = M.b0[t * NH + jt * 16 + i16];
-        acc[jt] = acc_t{b0, b0, b0, b0};
-    }
-    {
-        // this lane's 26 descriptor values, all loads in flight at once
-        real qa[KD / 4];
+        for (int x = 0; x < H0; x++) {
+            if (d0 + x >= NT) continue;
+            if constexpr (f64) {
 #pragma unroll
-        for (int ks = 0; ks < KD / 4; ks++) qa[ks] = rv ? qrow[ks * 4 + kq] : real(0);
-#pragma unroll
-        for (int ks = 0; ks < KD / 4; ks++) {
-#pragma unroll
-            for (int jt = 0; jt < 4; jt++)
-                acc[jt] = MF<real>::mma(qa[ks], sW[(ks * 4 + kq) * WLD + jt * 16 + i16], acc[jt]);
-        }
-    }
-    // activation, energy and the hidden-layer gradient
-    real e[4] = {0, 0, 0, 0};
-    real *g = sG + wave * 16 * GLD;
-#pragma unroll
-    for (int jt = 0; jt < 4; jt++) {
-        const real w = M.w1[t * NH + jt * 16 + i16];
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const real a = dtanh<real>(acc[jt][r]);
-            e[r] += w * a;
-            g[MF<real>::row(kq, r) * GLD + jt * 16 + i16] = w * (real(1) - a * a);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-#pragma unroll
-        for (int m = 1; m < 16; m <<= 1) e[r] += __shfl_xor(e[r], m);
-    }
-    if (i16 == 0) {
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int row = a0 + MF<real>::row(kq, r);
-            if (row < end && live(S, row) >= 0) W.Ei[row] = M.b1[t] + e[r];
-        }
-    }
-    __syncthreads();
-    // Fp = G W0: A[i][k] = G[i][k], B[k][j] = W0[k][j] = sW[j][k]
-    acc_t f[NT];
-#pragma unroll
-    for (int jt = 0; jt < NT; jt++) f[jt] = acc_t{0, 0, 0, 0};
-    for (int ks = 0; ks < NH / 4; ks++) {
-        const real a = g[i16 * GLD + ks * 4 + kq];
-#pragma unroll
-        for (int jt = 0; jt < NT; jt++) f[jt] = MF<real>::mma(a, sW[(jt * 16 + i16) * WLD + ks * 4 + kq], f[jt]);
-    }
-#pragma unroll
-    for (int jt = 0; jt < NT; jt++) {
-        const int col = jt * 16 + i16;
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int row = a0 + MF<real>::row(kq, r);
-            if (row < end && col < KD && live(S, row) >= 0) W.Fp[(size_t)row * DP + col] = f[jt][r];
+                for (int r = 0; r < 4; r++) {
+                    const int d = (d0 + x) * 16 + kq + 4 * r;
+                    if (d < KD) fp[d] = f[x][r];
+                }
+            } else {
+                const int d = (d0 + x) * 16 + 4 * kq;   // KD is a multiple of four
+                if (d < KD) *reinterpret_cast<float4 *>(fp + d) = make_float4(f[x][0], f[x][1], f[x][2], f[x][3]);
+            }
         }
     }
 }
@@ -1791,8 +1788,10 @@ void launch_mlp(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int 
     NEP_SPLIT(MLP_ATOMS)
     const int nb = mode == PASS_FULL ? nb_fe + nb_ge : nb_fe;
     if (!nb) return;
-    if (S.mag) hipLaunchKernelGGL((k_mlp<real, DP>), dim3(nb), dim3(64 * MLP_WAVES), 0, st, S, M, W, nb_fe);
-    else hipLaunchKernelGGL((k_mlp<real, DS_PAD>), dim3(nb), dim3(64 * MLP_WAVES), 0, st, S, M, W, nb_fe);
+    const dim3 g(nb), b(64 * MLP_WAVES);
+    if (!S.mag) hipLaunchKernelGGL((k_mlp<real, DS_PAD, false>), g, b, 0, st, S, M, W, nb_fe);
+    else if (mode == PASS_FULL) hipLaunchKernelGGL((k_mlp<real, DP, false>), g, b, 0, st, S, M, W, nb_fe);
+    else hipLaunchKernelGGL((k_mlp<real, DP, true>), g, b, 0, st, S, M, W, nb_fe);
 }
 
 template <typename real>
