@@ -463,22 +463,34 @@ constexpr int ANG_TS = 8 * ANG_TW + 1;   // per-atom stride (shifts LDS banks)
 
 // What the lanes of other atoms need of an atom: position, spin, box and
 // inverse box (zero on free axes), as doubles in LDS. Filled by its eight lanes.
+// A wavefront of these kernels lives for two to five rounds of pairs, two to four
+// wavefronts share a SIMD, and the latency of each dependent load of its
+// prologue (replica, counts, list entries, positions) costs about a round: so
+// all loads that do not depend on each other are issued before the first is
+// used, from the atom's own rows whether or not it turns out to be live.
 constexpr int AT_W = 12;
-__device__ inline void stage_atom(const Sys &S, const d4 *spin, int i, int lane, double *at) {
-    if (lane < 2) {
-        const d4 v = lane ? spin[i] : S.pos[i];
-        at[3 * lane] = v.x;
-        at[3 * lane + 1] = v.y;
-        at[3 * lane + 2] = v.z;
-    } else if (lane == 2) {
-        const Img g = img_of(S.rep[S.rid[i]]);
-#pragma unroll
-        for (int a = 0; a < 3; a++) {
-            at[6 + a] = g.b[a];
-            at[9 + a] = g.ib[a];
+struct AtomStage {
+    d4 v;             // position (lane 0), spin (lane 1)
+    double b;         // lanes 2-7: one component of the box or inverse box
+    bool active;
+    __device__ void load(const Sys &S, const d4 *spin, int i, int lane) {
+        const RepDev &R = S.rep[S.rid[i]];
+        const int c = max(lane - 2, 0), a = c < 3 ? c : c - 3;
+        v = (lane == 1 ? spin : S.pos)[i];
+        b = c < 3 ? R.box[a] : R.ibox[a];
+        if (!R.pbc[a]) b = 0;
+        active = R.active != 0;
+    }
+    __device__ void put(int lane, double *at) const {
+        if (lane < 2) {
+            at[3 * lane] = v.x;
+            at[3 * lane + 1] = v.y;
+            at[3 * lane + 2] = v.z;
+        } else {
+            at[4 + lane] = b;
         }
     }
-}
+};
 template <typename real>
 __device__ inline real geom_lds(const double *at, const d4 &pj, real d[3]) {
     const Img g = {{at[6], at[7], at[8]}, {at[9], at[10], at[11]}};
@@ -523,8 +535,20 @@ __device__ inline real dotc(const real *c, const real f[NB]) {
 
 // forward: per round, lanes stage eight neighbours of their atom (radial
 // functions g^A_n and (s_i.s_j) g^sa_n for all n, the 24 harmonics) in LDS,
-// then lane n accumulates A_nlm and B_nlm over the staged neighbours. B only
+// then the lanes accumulate A_nlm and B_nlm over the staged neighbours. B only
 // has spin-carrying pairs (spin-carrying centre, first phase).
+// A lane holds all n of six harmonics, 13 LDS values for 42 products (three
+// harmonics of A and B together would take 17). Where both A and B are
+// accumulated, lanes 0-3 take A and lanes 4-7 B; where one of them is, lanes
+// 0-3 take the even and lanes 4-7 the odd entries, and the two halves are added
+// afterwards: so the phase with A alone comes first. Lane 7 - q has the harmonics of lane q, so that the halves meet
+// under the mirrored-lane permutation. Lanes without a neighbour stage zeros:
+// the trip count is that of the wavefront and the loop unrolls. The rounds of both
+// phases form one sequence, loaded ahead across the phases' border.
+// FP64 is bound by latency at the two wavefronts per SIMD that the accumulators
+// and the tile allow (VALU 49 %, LDS 46 % busy), FP32 by VALU issue.
+// 262,144 atoms, mean of the three passes of a step: FP64 236 -> 220 us, FP32
+// 143 -> 124; 2,097,152 atoms, FP64: 1.86 -> 1.75 ms.
 // Pass modes: PASS_FULL stores A (all atoms) and B (spin carriers) for the
 // backward pass; PASS_SPIN (spin carriers only) stores A for the coupling
 // assembly; PASS_SPIN_REUSE (same positions as the preceding PASS_SPIN)
@@ -533,70 +557,75 @@ template <typename real>
 __device__ __forceinline__ void desc_angular(const Sys &S, const real *__restrict__ C, const Work<real> &W,
                                              const d4 *spin, int nbFe, int mode) {
     __shared__ real tile[ANG_ATOMS * ANG_TS];
-    __shared__ int smax[2];
     const int lane = threadIdx.x & 7, slot = threadIdx.x >> 3;
     bool fe;
-    const int i = live(S, atom_of_block(S, blockIdx.x, ANG_ATOMS, nbFe, slot, fe));
-    const bool reuse = mode == PASS_SPIN_REUSE;
-    if (threadIdx.x == 0) smax[0] = smax[1] = 0;
-    __syncthreads();
-    int cnt = 0, nfe = 0;
-    d4 pi = {0, 0, 0, 0};
-    real si[3] = {0, 0, 0};
-    Img R = {};
-    if (i >= 0) {
-        cnt = S.cntA[i];
-        nfe = S.cntFeA[i];
-        pi = S.pos[i];
-        load_spin(spin, i, si);
-        R = img_of(S.rep[S.rid[i]]);
-        if (lane == 0) {
-            atomicMax(&smax[0], nfe);
-            atomicMax(&smax[1], cnt - nfe);
-        }
+    const int i0 = atom_of_block(S, blockIdx.x, ANG_ATOMS, nbFe, slot, fe), ii = max(i0, 0);
+    const bool reuse = mode == PASS_SPIN_REUSE, mag = S.mag && fe;
+    const int *row = S.actA + (size_t)ii * MAXA;
+    const d4 pi = S.pos[ii];
+    real si[3];
+    load_spin(spin, ii, si);
+    int cnt = S.cntA[ii], nfe = S.cntFeA[ii];
+    const RepDev &rep = S.rep[S.rid[ii]];
+    const Img R = img_of(rep);
+    const int i = i0 >= 0 && rep.active ? i0 : -1;
+    if (i < 0) cnt = nfe = 0;
+    // most pairs of an atom of the wavefront, by phase
+    int most0 = 0, most1 = 0;
+#pragma unroll
+    for (int k = 0; k < ANG_ATOMS; k++) {
+        const int f = __builtin_amdgcn_readlane(nfe, 8 * k);
+        most0 = max(most0, f);
+        most1 = max(most1, __builtin_amdgcn_readlane(cnt, 8 * k) - f);
     }
-    __syncthreads();
+    if (reuse) most1 = 0;
     const int n = lane < NA ? lane : NA - 1;
-    const int m0 = 3 * lane;                 // this lane's three harmonics, for every n
+    const int h = lane >> 2, m0 = 6 * (h ? 7 - lane : lane);
     const real rc = (real)RC_A;
-    const int *row = S.actA + (size_t)(i < 0 ? 0 : i) * MAXA;
-    real A[NA][3], B[NA][3];
+    real acc[NA][6];
 #pragma unroll
     for (int x = 0; x < NA; x++)
 #pragma unroll
-        for (int m = 0; m < 3; m++) A[x][m] = B[x][m] = 0;
+        for (int m = 0; m < 6; m++) acc[x][m] = 0;
     real *my = tile + slot * ANG_TS;
-    const int nparts = reuse ? 1 : 2;
-    for (int part = 0; part < nparts; part++) {
+    // rounds of the first phase, then of the second: this lane's neighbour
+    // index two rounds ahead, its position and spin one round ahead
+    const int rd1 = (most1 + 7) >> 3, rds = rd1 + ((most0 + 7) >> 3);
+    const auto slot_of = [&](int rd) { return rd < rd1 ? nfe + 8 * rd + lane : 8 * (rd - rd1) + lane; };
+    const auto end_of = [&](int rd) { return rd < rd1 ? cnt : nfe; };
+    const auto index_of = [&](int rd, int other) { return slot_of(rd) < end_of(rd) ? row[slot_of(rd)] : other; };
+    int jc = index_of(0, ii), jn = index_of(1, jc);
+    d4 pc = S.pos[jc], vc = {0, 0, 0, 0};
+    if (mag) vc = spin[jc];
+    const auto phase = [&](const int part, int rd, const int rd_end, const int most) {
         const int tau = (fe ? 0 : 2) + part;
         const real *cA = C + P_CA + tau * NA * NB, *cS = C + P_CSA + tau * NA * NB;
-        const bool spins = S.mag && fe && part == 0;
-        const int b = part ? nfe : 0, e = part ? cnt : nfe;
-        const int rounds = (smax[part] + 7) >> 3;
-        // this lane's neighbour index two rounds ahead, position and spin one round ahead
-        const int s0 = b + lane;
-        int jc = s0 < e ? row[s0] : 0;
-        int jn = s0 + 8 < e ? row[s0 + 8] : jc;
-        d4 pc = S.pos[jc], vc = {0, 0, 0, 0};
-        if (spins) vc = spin[jc];
-        for (int rd = 0; rd < rounds; rd++) {
-            const int s = b + rd * 8 + lane;
+        const bool spins = mag && part == 0, both = spins && !reuse;
+        const int rd0 = rd;
+        for (; rd < rd_end; rd++) {
+            const bool on = slot_of(rd) < end_of(rd);
             const d4 pj = pc, vj = vc;
             jc = jn;
             pc = S.pos[jc];
-            if (spins) vc = spin[jc];
-            if (s + 16 < e) jn = row[s + 16];
+            if (mag && rd + 1 >= rd1) vc = spin[jc];
+            jn = index_of(rd + 2, jc);
             real *en = my + lane * ANG_TW;
-            if (s < e) {
+            {
                 real d[3];
-                const real r2 = geom_p(R, pi, pj, d);
+                real r2 = geom_p(R, pi, pj, d);
+                if (!on) {   // any finite geometry; its radial functions are zeroed
+                    d[0] = r2 = 1;
+                    d[1] = d[2] = 0;
+                }
                 real r, ir;
                 r_and_inv(r2, r, ir);
                 real f[NB];
                 radial_basis(r, rc, f);
+#pragma unroll
+                for (int k = 0; k < NB; k++) f[k] = on ? f[k] : real(0);
                 if (spins) {
                     const real sj[3] = {(real)vj.x, (real)vj.y, (real)vj.z};
-                    const real sig = si[0] * sj[0] + si[1] * sj[1] + si[2] * sj[2];
+                    const real sig = on ? si[0] * sj[0] + si[1] * sj[1] + si[2] * sj[2] : real(0);
 #pragma unroll
                     for (int nn = 0; nn < NA; nn++) en[NA + nn] = sig * dotc(cS + nn * NB, f);
                 }
@@ -610,67 +639,56 @@ __device__ __forceinline__ void desc_angular(const Sys &S, const real *__restric
                 for (int m = 0; m < NLM; m++) en[2 * NA + m] = Y[m];
             }
             __syncthreads();
-            const int qn = min(8, e - (b + rd * 8));
-            if (spins && !reuse) {
-                for (int q = 0; q < qn; q++) {
-                    const real *e2 = my + q * ANG_TW;
-                    const real y0 = e2[2 * NA + m0], y1 = e2[2 * NA + m0 + 1], y2 = e2[2 * NA + m0 + 2];
+            // this lane's entries: all, or those of its half
+            const real *eg = my + (both ? h * NA : (h ? ANG_TW : 0) + (reuse ? NA : 0));
+            const real *ey = my + (both ? 0 : (h ? ANG_TW : 0)) + 2 * NA + m0;
+            const int step = both ? ANG_TW : 2 * ANG_TW;
+            const int left = min(8, most - 8 * (rd - rd0)), trips = both ? left : (left + 1) >> 1;
+#pragma unroll 2
+            for (int q = 0; q < trips; q++) {
+                real y[6];
 #pragma unroll
-                    for (int x = 0; x < NA; x++) {
-                        const real ga = e2[x], gs = e2[NA + x];
-                        A[x][0] += ga * y0;
-                        A[x][1] += ga * y1;
-                        A[x][2] += ga * y2;
-                        B[x][0] += gs * y0;
-                        B[x][1] += gs * y1;
-                        B[x][2] += gs * y2;
-                    }
-                }
-            } else if (spins) {
-                for (int q = 0; q < qn; q++) {
-                    const real *e2 = my + q * ANG_TW;
-                    const real y0 = e2[2 * NA + m0], y1 = e2[2 * NA + m0 + 1], y2 = e2[2 * NA + m0 + 2];
+                for (int m = 0; m < 6; m++) y[m] = ey[q * step + m];
 #pragma unroll
-                    for (int x = 0; x < NA; x++) {
-                        const real gs = e2[NA + x];
-                        B[x][0] += gs * y0;
-                        B[x][1] += gs * y1;
-                        B[x][2] += gs * y2;
-                    }
-                }
-            } else {
-                for (int q = 0; q < qn; q++) {
-                    const real *e2 = my + q * ANG_TW;
-                    const real y0 = e2[2 * NA + m0], y1 = e2[2 * NA + m0 + 1], y2 = e2[2 * NA + m0 + 2];
+                for (int x = 0; x < NA; x++) {
+                    const real g = eg[q * step + x];
 #pragma unroll
-                    for (int x = 0; x < NA; x++) {
-                        const real ga = e2[x];
-                        A[x][0] += ga * y0;
-                        A[x][1] += ga * y1;
-                        A[x][2] += ga * y2;
-                    }
+                    for (int m = 0; m < 6; m++) acc[x][m] += g * y[m];
                 }
             }
             __syncthreads();
         }
-    }
+        if (!both) {   // the halves added, the first keeps the sum; the last phase leaves it in both
+#pragma unroll
+            for (int x = 0; x < NA; x++)
+#pragma unroll
+                for (int m = 0; m < 6; m++) {
+                    acc[x][m] += dpp<0x141>(acc[x][m]);   // row_half_mirror
+                    if (part && h) acc[x][m] = 0;
+                }
+        }
+    };
+    if (!reuse) phase(1, 0, rd1, most1);
+    phase(0, rd1, rds, most0);
     // regroup through LDS: lane n takes A_n and B_n over all 24 harmonics
     real An[NLM], Bn[NLM];
-    if (!reuse) {
+    if (h == 0) {
 #pragma unroll
         for (int x = 0; x < NA; x++)
 #pragma unroll
-            for (int m = 0; m < 3; m++) my[x * NLM + m0 + m] = A[x][m];
-        __syncthreads();
-#pragma unroll
-        for (int m = 0; m < NLM; m++) An[m] = my[n * NLM + m];
-        __syncthreads();
+            for (int m = 0; m < 6; m++) my[x * NLM + m0 + m] = acc[x][m];
     }
-    if (fe && S.mag) {
+    __syncthreads();
 #pragma unroll
-        for (int x = 0; x < NA; x++)
+    for (int m = 0; m < NLM; m++) An[m] = my[n * NLM + m];
+    __syncthreads();
+    if (mag && !reuse) {
+        if (h) {
 #pragma unroll
-            for (int m = 0; m < 3; m++) my[x * NLM + m0 + m] = B[x][m];
+            for (int x = 0; x < NA; x++)
+#pragma unroll
+                for (int m = 0; m < 6; m++) my[x * NLM + m0 + m] = acc[x][m];
+        }
         __syncthreads();
 #pragma unroll
         for (int m = 0; m < NLM; m++) Bn[m] = my[n * NLM + m];
@@ -683,7 +701,10 @@ __device__ __forceinline__ void desc_angular(const Sys &S, const real *__restric
     real *q = W.q + (size_t)i * DP;
     if (reuse) {
 #pragma unroll
-        for (int m = 0; m < NLM; m++) An[m] = ab[m];
+        for (int m = 0; m < NLM; m++) {
+            Bn[m] = An[m];
+            An[m] = ab[m];
+        }
     }
     real qa[4] = {0, 0, 0, 0}, qs[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -700,7 +721,7 @@ __device__ __forceinline__ void desc_angular(const Sys &S, const real *__restric
 #pragma unroll
         for (int m = 0; m < NLM; m++) ab[m] = An[m];
     }
-    if (fe && S.mag && mode == PASS_FULL) {   // B only for the spin-carrying backward
+    if (mag && mode == PASS_FULL) {   // B only for the spin-carrying backward
 #pragma unroll
         for (int m = 0; m < NLM; m++) ab[NLM + m] = Bn[m];
     }
@@ -1279,11 +1300,13 @@ __global__ void __launch_bounds__(256) k_bwd_mag(Sys S, Work<real> W) {
 // -------------------------------------------------------------------------
 
 // What bounds it: FP64 issue and the LDS reads of QA/QS (14 per harmonic and
-// pair), both per lane slot. With the neighbours dealt eight per atom and round
-// from the Verlet rows only 60 % of the slots held a pair inside the cutoff;
-// the flat in-cutoff pairs fill 90 %:
+// pair), both per lane slot, and the load latencies at the start. With the
+// neighbours dealt eight per atom and round from the Verlet rows only 60 % of the
+// slots held a pair inside the cutoff; the flat in-cutoff pairs fill 90 %:
 // 2,097,152 atoms, FP64, carriers 4.45 -> 3.49 ms per launch, the others 2.75 -> 2.10;
-// 1,048,576 atoms, FP32, 1.23 -> 0.98 and 0.91 -> 0.63 ms.
+// 1,048,576 atoms, FP32, 1.23 -> 0.98 and 0.91 -> 0.63 ms. With the prologue's
+// loads issued together and the spins loaded a round ahead: 2.82 and 1.78 ms;
+// 0.72 and 0.48 ms.
 
 // Each species runs as its own launch over atoms [first, last). Atoms without
 // spin work (the second species, or every atom of a structural-only model)
@@ -1299,28 +1322,24 @@ __device__ __forceinline__ void bwd_angular(const Sys &S, const real *__restrict
     const int tid = threadIdx.x, lane = tid & 7, slot = tid >> 3;
     const bool fe = first < S.N_fe;    // species 0: the pair types tau = 0, 1
     const int i0 = first + block * ANG_ATOMS;
-    const int i = live(S, i0 + slot < last ? i0 + slot : -1);
-    int cnt = 0, nfe = 0;
-    if (i >= 0) {
-        real *Q = sQ + slot * QSTRIDE;   // QA[n][m], then QS[n][m] on spin carriers
-        const real *Fp = W.Fp + (size_t)i * DP;
-        for (int x = lane; x < NA * NLM; x += 8) {
-            const int n = x / NLM, m = x - n * NLM, l = l_of_lm(m) - 1;
-            const real *ab = W.AB + ((size_t)i * NA + n) * NAB;
-            const real fa = Fp[D_A + 4 * n + l];
-            if (FE) {
-                const real fs = Fp[D_SA + 4 * n + l];
-                Q[x] = real(2) * fa * ab[m] + fs * ab[NLM + m];
-                Q[NA * NLM + x] = fs * ab[m];
-            } else {
-                Q[x] = real(2) * fa * ab[m];
-            }
+    // every load of the prologue before the first use of one: a wavefront has
+    // four rounds, and the latency of a chain of loads costs as much as one
+    const int ii = min(i0 + slot, last - 1);
+    const int cnt_i = S.cntA[ii], nfe_i = S.cntFeA[ii];
+    AtomStage as;
+    as.load(S, S.spin, ii, lane);
+    constexpr int QL = NA * NLM / 8;     // this lane's harmonics: 8 (k % 3) + lane of n = k / 3
+    real av[QL], bv[FE ? QL : 1];
+    {
+        const real *ab = W.AB + (size_t)ii * NA * NAB + lane;
+#pragma unroll
+        for (int k = 0; k < QL; k++) {
+            av[k] = ab[k / 3 * NAB + 8 * (k % 3)];
+            if (FE) bv[k] = ab[k / 3 * NAB + NLM + 8 * (k % 3)];
         }
-        stage_atom(S, S.spin, i, lane, sAt + slot * AT_W);
-        cnt = S.cntA[i];
-        nfe = S.cntFeA[i];
     }
-    __syncthreads();
+    const int i = i0 + slot < last && as.active ? ii : -1;
+    const int cnt = i >= 0 ? cnt_i : 0, nfe = i >= 0 ? nfe_i : 0;
     const real rc = (real)RC_A;
     const size_t ld = S.N;
     real Fo[3] = {0, 0, 0}, ho[3] = {0, 0, 0};     // own-side sums of this lane's pairs
@@ -1330,7 +1349,7 @@ __device__ __forceinline__ void bwd_angular(const Sys &S, const real *__restrict
     fl.set(nfe);
     int off0 = fl.own(slot), off1 = 0;
     int na = -1, nj = 0, nsr = 0;
-    d4 np = {0, 0, 0, 0};
+    d4 np = {0, 0, 0, 0}, ns = {0, 0, 0, 0};
     auto next = [&]() {
         na = -1;
         if (rn >= fl.off[ANG_ATOMS] && pn == 0) {
@@ -1341,22 +1360,42 @@ __device__ __forceinline__ void bwd_angular(const Sys &S, const real *__restrict
         }
         if (rn >= fl.off[ANG_ATOMS]) return;       // no round left
         const int p = rn + tid;
+        int o;
+        const int q = fl.find(p, o), lead = __shfl(nfe, 8 * q);
         if (p < fl.off[ANG_ATOMS]) {
-            int o;
-            na = fl.find(p, o);
-            const size_t x = (size_t)(i0 + na) * MAXA + (p - o) + (pn ? S.cntFeA[i0 + na] : 0);
+            na = q;
+            const size_t x = (size_t)(i0 + na) * MAXA + (p - o) + (pn ? lead : 0);
             nj = S.actA[x];
             nsr = S.actS[x];
             np = S.pos[nj];
+            if (FE && pn == 0) ns = S.spin[nj];
         }
     };
     next();
+    if (i >= 0) {
+        real *Q = sQ + slot * QSTRIDE;   // QA[n][m], then QS[n][m] on spin carriers
+        const real *Fp = W.Fp + (size_t)i * DP;
+        const int l3[3] = {l_of_lm(lane) - 1, l_of_lm(8 + lane) - 1, l_of_lm(16 + lane) - 1};
+#pragma unroll
+        for (int k = 0; k < QL; k++) {
+            const int x = 8 * k + lane, nl = 4 * (k / 3) + l3[k % 3];
+            if (FE) {
+                const real fa = Fp[D_A + nl], fs = Fp[D_SA + nl];
+                Q[x] = real(2) * fa * av[k] + fs * bv[k];
+                Q[NA * NLM + x] = fs * av[k];
+            } else {
+                Q[x] = real(2) * Fp[D_A + nl] * av[k];
+            }
+        }
+        as.put(lane, sAt + slot * AT_W);
+    }
+    __syncthreads();
     // rounds of 64 pairs of the eight atoms, spin-carrying neighbours first
 #pragma unroll 1
     while (rn < fl.off[ANG_ATOMS]) {
         const int part = pn, r0 = rn, T = fl.off[ANG_ATOMS];
         const int a = na, j = nj, sr = nsr;
-        const d4 pj = np;
+        const d4 pj = np, vj = ns;
         rn += 64;
         next();
         const int tau = (fe ? 0 : 2) + part;
@@ -1374,7 +1413,9 @@ __device__ __forceinline__ void bwd_angular(const Sys &S, const real *__restrict
             radial_basis_d(r, rc, f, df);
             real sig = 0;
             if (spins) {
-                load_spin(S.spin, j, sj);
+                sj[0] = (real)vj.x;
+                sj[1] = (real)vj.y;
+                sj[2] = (real)vj.z;
                 sig = (real)at[3] * sj[0] + (real)at[4] * sj[1] + (real)at[5] * sj[2];
             }
             real gA[NA], dgA[NA], gS[NA], dgS[NA];
@@ -1548,7 +1589,9 @@ __global__ void __launch_bounds__(256) k_gather(Sys S, Work<real> W) {
 // -------------------------------------------------------------------------
 
 // spin-angular part of a_ij: sum_n g^sa_n(r_ij) sum_lm Fp^sa_nl A_nlm Y_lm(rhat_ij);
-// a lane per pair of the wavefront's eight spins, P = Fp^sa A in LDS
+// a lane per pair of the wavefront's eight spins, P = Fp^sa A in LDS. Two rounds
+// of pairs per wavefront: its time is that of the prologue's loads, issued
+// together (2,097,152 atoms, FP64: 1.02 -> 0.66 ms; 262,144: 146 -> 90 us).
 constexpr int PSTRIDE = NA * NLM + 1;
 
 template <typename real>
@@ -1557,20 +1600,20 @@ __global__ void __launch_bounds__(64) k_assemble_angular(Sys S, const real *__re
     __shared__ double sAt[ANG_ATOMS * AT_W];
     const int tid = threadIdx.x, lane = tid & 7, slot = tid >> 3;
     const int i0 = blockIdx.x * ANG_ATOMS;
-    const int i = live(S, i0 + slot < S.N_fe ? i0 + slot : -1);
-    const real *cS = C + P_CSA;   // tau = (Fe, Fe)
-    int nfe = 0;
-    if (i >= 0) {
-        real *P = sP + slot * PSTRIDE;
-        const real *Fp = W.Fp + (size_t)i * DP;
-        for (int x = lane; x < NA * NLM; x += 8) {
-            const int n = x / NLM, m = x - n * NLM;
-            P[x] = Fp[D_SA + 4 * n + l_of_lm(m) - 1] * W.AB[((size_t)i * NA + n) * NAB + m];
-        }
-        stage_atom(S, S.spin, i, lane, sAt + slot * AT_W);
-        nfe = S.cntFeA[i];
+    const int ii = min(i0 + slot, S.N_fe - 1);
+    const int nfe_i = S.cntFeA[ii];     // the prologue's loads together, as in the backward pass
+    AtomStage as;
+    as.load(S, S.spin, ii, lane);
+    constexpr int QL = NA * NLM / 8;
+    real av[QL];
+    {
+        const real *ab = W.AB + (size_t)ii * NA * NAB + lane;
+#pragma unroll
+        for (int k = 0; k < QL; k++) av[k] = ab[k / 3 * NAB + 8 * (k % 3)];
     }
-    __syncthreads();
+    const int i = i0 + slot < S.N_fe && as.active ? ii : -1;
+    const int nfe = i >= 0 ? nfe_i : 0;
+    const real *cS = C + P_CSA;   // tau = (Fe, Fe)
     const real rc = (real)RC_A;
     const size_t lf = S.N_fe;
     Flat8 fl;
@@ -1589,6 +1632,15 @@ __global__ void __launch_bounds__(64) k_assemble_angular(Sys S, const real *__re
         }
     };
     next(tid);
+    if (i >= 0) {
+        real *P = sP + slot * PSTRIDE;
+        const real *Fp = W.Fp + (size_t)i * DP + D_SA;
+        const int l3[3] = {l_of_lm(lane) - 1, l_of_lm(8 + lane) - 1, l_of_lm(16 + lane) - 1};
+#pragma unroll
+        for (int k = 0; k < QL; k++) P[8 * k + lane] = Fp[4 * (k / 3) + l3[k % 3]] * av[k];
+        as.put(lane, sAt + slot * AT_W);
+    }
+    __syncthreads();
 #pragma unroll 1
     for (int r0 = 0; r0 < fl.off[ANG_ATOMS]; r0 += 64) {
         const int at = na, s = ns;
