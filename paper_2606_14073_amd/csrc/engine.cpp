@@ -260,6 +260,7 @@ struct Engine {
     size_t cap_obs = 0, cap_col = 0;
     int n_chunks = 0;
     std::vector<int> col_ptr;
+    int lds_spins = 0;          // spins of the largest replica where each one's sweep runs in a workgroup, else 0
 
     // kernel-group timing (sl_profile_enable)
     unsigned prof_mask = 0;
@@ -655,6 +656,16 @@ struct Engine {
         h_cptr.push_back((int)h_chunks.size());
         n_cells = cb;
         n_chunks = (int)h_chunks.size();
+        int64_t most = 0;
+        bool coloured = true;   // false only where nothing is swept
+        for (const Replica *r : reps) {
+            most = std::max<int64_t>(most, r->n_fe);
+            coloured = coloured && (int64_t)r->colour_fe.size() == r->n_fe;
+        }
+        lds_spins = most <= (prec == SL_FP64 ? sweep_lds_spins<double>() : sweep_lds_spins<float>()) &&
+                            coloured && cmax <= SWEEP_LDS_COLOURS && reps.size() <= SWEEP_LDS_REPLICAS
+                        ? (int)most
+                        : 0;
         // colour classes
         // (counting sort: inside a colour, replica order, then atom order)
         col_ptr.assign(cmax + 1, 0);
@@ -865,7 +876,7 @@ struct Engine {
             }
             {
                 ProfScope q(this, 7);
-                launch_sweep(S, w, col_ptr.data(), (int)col_ptr.size() - 1, st);
+                launch_sweep(S, w, col_ptr.data(), (int)col_ptr.size() - 1, lds_spins, st);
             }
             passes = p + 1;
             if (sc) {

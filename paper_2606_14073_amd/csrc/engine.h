@@ -18,6 +18,15 @@ constexpr int MAXFE = 64;     // listed spin-carrying neighbours kept for the sp
 constexpr int WIDE_LANES = 8;
 constexpr long long WIDE_MAX_ATOMS = 65536;
 
+// A batch whose replicas all have at most so many spins is swept by a workgroup
+// per replica instead of a launch per colour class (both sides at k_sweep_lds; the
+// bits are the same), as long as there is a CU for each: a CU's registers hold
+// one such workgroup.
+template <typename real>
+constexpr int sweep_lds_spins() { return sizeof(real) == 8 ? 900 : 1300; }
+constexpr int SWEEP_LDS_COLOURS = 256;
+constexpr int SWEEP_LDS_REPLICAS = 256;
+
 constexpr int RCOEF = 4 * NB; // per-atom contracted radial-set coefficients
 constexpr int MCOEF = 3 * NB; // per-spin-carrier contracted magnetic pair coefficients
 
@@ -132,7 +141,8 @@ void launch_assemble_coef(const Sys &S, const ModelDev<real> &M, const Work<real
 template <typename real>
 void launch_assemble_pairs(const Sys &S, const ModelDev<real> &M, const Work<real> &W, hipStream_t st);
 template <typename real>
-void launch_sweep(const Sys &S, const Work<real> &W, const int *col_ptr_host, int n_colours, hipStream_t st);
+void launch_sweep(const Sys &S, const Work<real> &W, const int *col_ptr_host, int n_colours, int lds_spins,
+                  hipStream_t st);
 
 void launch_kick(const Sys &S, hipStream_t st);
 void launch_drift(const Sys &S, hipStream_t st);   // also refreshes pos4

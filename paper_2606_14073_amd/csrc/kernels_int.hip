@@ -208,6 +208,7 @@ __device__ inline void coupling_field(double J, double D, double K, double rx, d
 constexpr int SWEEP_V = 16;              // virtual lanes of the field sum
 constexpr int SWEEP_WIDE_MIN = 8192;     // classes of at least this many spins take 8 lanes per spin
 constexpr int SWEEP_WIDER_MIN = 32768;   // and of at least this many 4
+constexpr int SWEEP_LDS_THREADS = 512;   // workgroup of a replica whose spins stay in LDS
 
 // what a visit needs that does not depend on the neighbours' spins: everything
 // indexed by the colour-list position p (atom, coupling count, self terms, the
@@ -243,10 +244,10 @@ struct SweepSpin {
     }
 };
 
-// the field of the neighbours on the spin, summed over its lanes
-template <typename real, int L>
-__device__ inline void sweep_field(const Sys &S, const Work<real> &W, const SweepSpin<real, L> &q, int lane, double &hx,
-                                   double &hy, double &hz) {
+// the field of the neighbours on the spin, summed over its lanes; at(j) is spin j
+template <typename real, int L, typename At>
+__device__ inline void sweep_field(const Sys &S, const Work<real> &W, const SweepSpin<real, L> &q, int lane, At at,
+                                   double &hx, double &hy, double &hz) {
 #pragma clang fp contract(off)
     constexpr int P = SweepSpin<real, L>::P, R0 = SweepSpin<real, L>::R0;
     const size_t lf = S.N_fe;
@@ -256,7 +257,7 @@ __device__ inline void sweep_field(const Sys &S, const Work<real> &W, const Swee
     d4 sj[R0];
 #pragma unroll
     for (int u = 0; u < R0; u++)
-        sj[u] = S.spin[lane + L * (u >> 1) + SWEEP_V * (u & 1) < q.nc ? q.cj[u] : q.i];
+        sj[u] = at(lane + L * (u >> 1) + SWEEP_V * (u & 1) < q.nc ? q.cj[u] : q.i);
 #pragma unroll
     for (int u = 0; u < R0; u++) {
         const int k = u >> 1;
@@ -270,7 +271,7 @@ __device__ inline void sweep_field(const Sys &S, const Work<real> &W, const Swee
         for (int s = lane + L * k + 2 * SWEEP_V; s < q.nc; s += SWEEP_V) {
             const int j = W.cpl_j[(size_t)s * lf + q.p];
             const real *c = W.cpl + ((size_t)s * lf + q.p) * 6;
-            const d4 v = S.spin[j];
+            const d4 v = at(j);
             coupling_field(c[0], c[1], c[2], c[3], c[4], c[5], v.x, v.y, v.z, px[k], py[k], pz[k]);
         }
     // butterfly: levels 1 .. L/2 across the lanes, then L .. 8 inside them
@@ -555,12 +556,97 @@ __global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, in
     const RepDev &R = S.rep[r];
     if (!spin_pass_on(R)) return;
     double hx, hy, hz, yx, yy, yz;
-    sweep_field<real, L>(S, W, q, lane, hx, hy, hz);
+    sweep_field<real, L>(S, W, q, lane, [&](int j) { return S.spin[j]; }, hx, hy, hz);
     const int ncapped = sweep_solve(R, sweep_const(R), q, (uint32_t)S.orig[q.i], lane, turns, visit0, hx, hy, hz, yx, yy, yz);
     if (lane == 0) {
         S.spin[q.i] = d4{yx, yy, yz, 0.0};
         if (ncapped) atomicAdd(&S.rep[r].capped, ncapped);
     }
+}
+
+// The whole sweep of a replica in one workgroup, its spins in LDS: the colour
+// classes follow each other after a barrier, and the couplings of the next
+// class's first spins are loaded while this one's are solved, so that a class
+// costs its field sum and its solve, 3.3 us, without the launch, the loads and
+// the spins' way through memory (5.1 us and the gap to the next launch). What
+// bounds it is the chain of about 1,200 dependent instructions of a visit.
+// FP64 takes 16 lanes per spin; FP32 couplings leave registers for the eight
+// that suit more spins per class. 512 atoms, whole step, FP64 986 -> 756 us,
+// FP32 929 -> 665; 1,728 atoms 1,104 -> 1,009 and 1,021 -> 771. A larger replica
+// needs several rounds of spins per class in its one workgroup and is slower
+// than by class launches: FP64 2,744 atoms 999 -> 1,265 us; FP32 2,744 atoms
+// 908 -> 902, 4,096 atoms 1,048 -> 1,080.
+template <typename real>
+__global__ void __launch_bounds__(SWEEP_LDS_THREADS) k_sweep_lds(Sys S, Work<real> W) {
+    constexpr int L = sizeof(real) == 8 ? 16 : 8;
+    extern __shared__ double sp[];   // [n_fe][3]
+    __shared__ int c0[SWEEP_LDS_COLOURS], c1[SWEEP_LDS_COLOURS], sn[2];   // a colour's list positions; colours, capped
+    constexpr int PER = SWEEP_LDS_THREADS / L;
+    const int tid = threadIdx.x, lane = tid & (L - 1), t = tid / L, rid = blockIdx.x;
+    const RepDev &R = S.rep[rid];
+    if (!spin_pass_on(R)) return;
+    const int n = R.n_fe, off = R.fe_off;
+    for (int c = tid; c < SWEEP_LDS_COLOURS; c += SWEEP_LDS_THREADS) c0[c] = c1[c] = 0;
+    if (tid < 2) sn[tid] = 0;
+    __syncthreads();
+    // inside a colour the list holds the replica's spins one after the other
+    for (int a = tid; a < n; a += SWEEP_LDS_THREADS) {
+        const int p = S.colpos[off + a], c = S.colour[off + a];
+        const d4 v = S.spin[off + a];
+        sp[3 * a] = v.x;
+        sp[3 * a + 1] = v.y;
+        sp[3 * a + 2] = v.z;
+        if (p == 0 || S.col_rid[p - 1] != rid || S.colour[S.col_idx[p - 1]] != c) {
+            c0[c] = p;
+            atomicMax(&sn[0], c + 1);
+        }
+        if (p + 1 == S.N_fe || S.col_rid[p + 1] != rid || S.colour[S.col_idx[p + 1]] != c) c1[c] = p + 1;
+    }
+    __syncthreads();
+    const int ncol = sn[0], steps = 2 * ncol - 1;
+    const SweepConst k = sweep_const(R);
+    const auto class_of = [&](int step) { return step < ncol ? step : 2 * ncol - 2 - step; };
+    const auto at = [&](int j) {
+        const double *v = sp + 3 * (j - off);
+        return d4{v[0], v[1], v[2], 0.0};
+    };
+    SweepSpin<real, L> nx;
+    nx.i = off;
+    if (steps > 0 && c0[0] + t < c1[0]) {
+        nx.load(S, W, lane, c0[0] + t);
+        nx.e = S.eta[nx.i];
+    }
+    int ncapped = 0;
+    for (int step = 0; step < steps; step++) {
+        const int c = class_of(step), cn = class_of(min(step + 1, steps - 1));
+        const int turns = step == ncol - 1 ? 2 : 1, visit0 = step < ncol ? 0 : 1, p1 = c1[c];
+        for (int p = c0[c] + t; p < p1; p += PER) {
+            SweepSpin<real, L> q = nx;
+            if (p + PER < p1) nx.load(S, W, lane, p + PER);
+            else if (c0[cn] + t < c1[cn]) nx.load(S, W, lane, c0[cn] + t);
+            q.s4 = at(q.i);
+            double hx, hy, hz, yx, yy, yz;
+            sweep_field<real, L>(S, W, q, lane, at, hx, hy, hz);
+            ncapped += sweep_solve(R, k, q, (uint32_t)S.orig[q.i], lane, turns, visit0, hx, hy, hz, yx, yy, yz);
+            nx.e = S.eta[nx.i];
+            if (lane == 0) {
+                double *v = sp + 3 * (q.i - off);
+                v[0] = yx;
+                v[1] = yy;
+                v[2] = yz;
+            }
+        }
+        // a lane group without a spin in this class
+        if (c0[c] + t >= p1 && c0[cn] + t < c1[cn]) {
+            nx.load(S, W, lane, c0[cn] + t);
+            nx.e = S.eta[nx.i];
+        }
+        __syncthreads();
+    }
+    if (lane == 0 && ncapped) atomicAdd(&sn[1], ncapped);
+    for (int a = tid; a < n; a += SWEEP_LDS_THREADS) S.spin[off + a] = d4{sp[3 * a], sp[3 * a + 1], sp[3 * a + 2], 0.0};
+    __syncthreads();
+    if (tid == 0 && sn[1]) atomicAdd(&S.rep[rid].capped, sn[1]);
 }
 
 // Re-layout of the resident replicas: atom k of the new layout takes the state
@@ -927,7 +1013,13 @@ void launch_sc_mix(const Sys &S, int pass, int depth, hipStream_t st) {
 // colours 0, 1, .., C-1 and then C-1, .., 0; the two visits of colour C-1 are
 // one launch
 template <typename real>
-void launch_sweep(const Sys &S, const Work<real> &W, const int *col_ptr_host, int n_colours, hipStream_t st) {
+void launch_sweep(const Sys &S, const Work<real> &W, const int *col_ptr_host, int n_colours, int lds_spins,
+                  hipStream_t st) {
+    if (lds_spins > 0) {
+        hipLaunchKernelGGL(k_sweep_lds<real>, dim3(S.n_rep), dim3(SWEEP_LDS_THREADS), 3 * sizeof(double) * lds_spins, st, S,
+                           W);
+        return;
+    }
     for (int pass = 0; pass < 2; pass++)
         for (int cc = 0; cc < n_colours; cc++) {
             if (pass == 1 && cc == 0) continue;       // done as the second turn of the last ascending launch
@@ -954,8 +1046,8 @@ void launch_observe(const Sys &S, const Work<real> &W, const Chunk *chunks, int 
     hipLaunchKernelGGL(k_obs_final, dim3(S.n_rep), dim3(256), 0, st, S, chunk_ptr, partial, out);
 }
 
-template void launch_sweep<double>(const Sys &, const Work<double> &, const int *, int, hipStream_t);
-template void launch_sweep<float>(const Sys &, const Work<float> &, const int *, int, hipStream_t);
+template void launch_sweep<double>(const Sys &, const Work<double> &, const int *, int, int, hipStream_t);
+template void launch_sweep<float>(const Sys &, const Work<float> &, const int *, int, int, hipStream_t);
 template void launch_observe<double>(const Sys &, const Work<double> &, const Chunk *, int, const int *, double *,
                                      double *, hipStream_t);
 template void launch_observe<float>(const Sys &, const Work<float> &, const Chunk *, int, const int *, double *,
