@@ -799,7 +799,8 @@ struct MlpLds<float> {
 // waited on scattered 4-byte reads and stores and on the LDS transposition of the
 // hidden tile. 2,097,152 atoms FP64, full pass 1.9 -> 1.43 ms, spin pass 0.95 ->
 // 0.61 (the products alone at the measured 71.8 TFLOP/s: 0.81 and 0.34);
-// 1,048,576 atoms FP32 0.60 -> 0.34 and 0.30 -> 0.17.
+// 1,048,576 atoms FP32 0.60 -> 0.33 and 0.30 -> 0.155. With the descriptor rows
+// loaded beside W0 instead of after it: 1.36 and 0.58; 0.27 and 0.134.
 template <typename real, int KD, bool SPIN>
 __global__ void __launch_bounds__(512) k_mlp(Sys S, ModelDev<real> M, Work<real> W, int nbFe) {
     typedef typename MF<real>::acc_t acc_t;
@@ -808,63 +809,68 @@ __global__ void __launch_bounds__(512) k_mlp(Sys S, ModelDev<real> M, Work<real>
     constexpr int KDT = (KD + 15) / 16 * 16, NT = KDT / 16;
     constexpr int T0 = SPIN ? D_OS / 16 : 0;   // first gradient tile
     __shared__ __align__(16) real sW[KDT * WLD];
+    __shared__ real sB[2 * NH];   // b0, w1
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const bool fe = (int)blockIdx.x < nbFe;
     const int t = fe ? 0 : 1;
     const int end = fe ? S.N_fe : S.N;
     const int a0 = (fe ? blockIdx.x * MLP_ATOMS : S.N_fe + (blockIdx.x - nbFe) * MLP_ATOMS) + wave * 16;
     const real *W0 = M.W0 + (size_t)t * DP * NH;
-    {
-        // all of the thread's values in flight at once
-        constexpr int SV = KDT * NH / (64 * MLP_WAVES);
-        static_assert(SV * 64 * MLP_WAVES == KDT * NH, "W0 is staged in whole rounds");
-        real w[SV];
-#pragma unroll
-        for (int v = 0; v < SV; v++) {
-            const int x = v * 64 * MLP_WAVES + threadIdx.x;
-            w[v] = x < KD * NH ? W0[x] : real(0);
-        }
-#pragma unroll
-        for (int v = 0; v < SV; v++) {
-            const int x = v * 64 * MLP_WAVES + threadIdx.x;
-            sW[(x / NH) * WLD + x % NH] = w[v];
-        }
-    }
-    __syncthreads();
+    // Every load of the kernel is issued here, before the first is used. The
+    // rows of atoms that are not live are read too: an atom is a column of both
+    // products, and what comes of theirs is not stored.
     const int i16 = lane & 15, kq = lane >> 4;
-    const int arow = a0 + i16;
-    const bool rv = arow < end && live(S, arow) >= 0;
-    const real *qrow = W.q + (size_t)(rv ? arow : 0) * DP;
-    // Z^T = W0 Q^T + b0. FP32 takes sixteen descriptor entries as four k-steps
-    // of four consecutive ones per lane quarter (one 16-byte load), the last
-    // eight as two of two.
+    const int arow = a0 + i16, row_in = min(arow, end - 1);
+    const RepDev &rep = S.rep[S.rid[row_in]];
+    const real *qrow = W.q + (size_t)row_in * DP;
+    // FP32 takes sixteen descriptor entries as four k-steps of four consecutive
+    // ones per lane quarter (one 16-byte load), the last eight as two of two.
     auto entry = [&](int ks) {
         if constexpr (f64) return ks * 4 + kq;
         else return ks < KD / 16 * 4 ? (ks >> 2) * 16 + 4 * kq + (ks & 3) : KD / 16 * 16 + 2 * kq + (ks & 1);
     };
+    constexpr int SV = KDT * NH / (64 * MLP_WAVES);
+    static_assert(SV * 64 * MLP_WAVES == KDT * NH, "W0 is staged in whole rounds");
+    real w0[SV];
+#pragma unroll
+    for (int v = 0; v < SV; v++) {
+        const int x = v * 64 * MLP_WAVES + threadIdx.x;
+        w0[v] = x < KD * NH ? W0[x] : real(0);
+    }
+    const real bw = threadIdx.x < NH ? M.b0[t * NH + threadIdx.x] : M.w1[t * NH + threadIdx.x % NH];
     real qa[KD / 4];
     if constexpr (f64) {
 #pragma unroll
-        for (int ks = 0; ks < KD / 4; ks++) qa[ks] = rv ? qrow[ks * 4 + kq] : real(0);
+        for (int ks = 0; ks < KD / 4; ks++) qa[ks] = qrow[ks * 4 + kq];
     } else {
         static_assert(KD % 16 == 8, "two k-steps after the sixteens");
 #pragma unroll
         for (int g = 0; g < KD / 16; g++) {
-            const float4 v = rv ? *reinterpret_cast<const float4 *>(qrow + 16 * g + 4 * kq) : make_float4(0, 0, 0, 0);
+            const float4 v = *reinterpret_cast<const float4 *>(qrow + 16 * g + 4 * kq);
             qa[4 * g] = v.x;
             qa[4 * g + 1] = v.y;
             qa[4 * g + 2] = v.z;
             qa[4 * g + 3] = v.w;
         }
-        const float2 v = rv ? *reinterpret_cast<const float2 *>(qrow + KD / 16 * 16 + 2 * kq) : make_float2(0, 0);
+        const float2 v = *reinterpret_cast<const float2 *>(qrow + KD / 16 * 16 + 2 * kq);
         qa[KD / 4 - 2] = v.x;
         qa[KD / 4 - 1] = v.y;
     }
+    const bool rv = arow < end && rep.active;
+    const real b1 = M.b1[t];
+#pragma unroll
+    for (int v = 0; v < SV; v++) {
+        const int x = v * 64 * MLP_WAVES + threadIdx.x;
+        sW[(x / NH) * WLD + x % NH] = w0[v];
+    }
+    if (threadIdx.x < 2 * NH) sB[threadIdx.x] = bw;
+    __syncthreads();
+    // Z^T = W0 Q^T + b0
     acc_t z[4];
 #pragma unroll
     for (int mt = 0; mt < 4; mt++)
 #pragma unroll
-        for (int r = 0; r < 4; r++) z[mt][r] = M.b0[t * NH + 16 * mt + MF<real>::row(kq, r)];
+        for (int r = 0; r < 4; r++) z[mt][r] = sB[16 * mt + MF<real>::row(kq, r)];
 #pragma unroll
     for (int ks = 0; ks < KD / 4; ks++) {
 #pragma unroll
@@ -877,7 +883,7 @@ __global__ void __launch_bounds__(512) k_mlp(Sys S, ModelDev<real> M, Work<real>
     for (int mt = 0; mt < 4; mt++)
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-            const real w = M.w1[t * NH + 16 * mt + MF<real>::row(kq, r)];
+            const real w = sB[NH + 16 * mt + MF<real>::row(kq, r)];
             const real a = dtanh<real>(z[mt][r]);
             e += w * a;
             g[mt][r] = w * (real(1) - a * a);
@@ -885,7 +891,7 @@ __global__ void __launch_bounds__(512) k_mlp(Sys S, ModelDev<real> M, Work<real>
     if (!SPIN) {
         e += __shfl_xor(e, 16);
         e += __shfl_xor(e, 32);
-        if (kq == 0 && rv) W.Ei[arow] = M.b1[t] + e;
+        if (kq == 0 && rv) W.Ei[arow] = b1 + e;
     }
     // Fp^T = W0^T G^T: A = W0^T tile from LDS, B = this lane's g; the
     // descriptor tiles in passes of at most four to bound the registers
