@@ -42,9 +42,9 @@ from paper_2606_14073_amd import workload as W  # noqa: E402
 # MI355X published peaks
 PEAK = {"fp64": 78.6, "fp32": 157.3, "hbm_gbs": 8000.0}
 KERNEL_NAME = {"desc_radial": "k_desc_radial<{r}>", "desc_angular": "k_desc_angular<{r}>",
-               "readout": "k_mlp<{r},104,false>", "bwd_radial": "k_bwd_radial<{r}>",
+               "readout": "k_mlp<{r},104,false,false>", "bwd_radial": "k_bwd_radial<{r}>",
                "bwd_angular": "k_bwd_angular<{r},true>", "bwd_angular_1": "k_bwd_angular<{r},false>",
-               "gather": "k_gather<{r}>", "couplings": "k_assemble_angular<{r}>", "pairs": "k_assemble_pairs<{r}>",
+               "gather": "k_gather<{r}>", "couplings": "k_assemble_angular<{r}>", "pairs": "k_assemble_pairs<{r},1>",
                "sweep": "k_sweep<{r}>", "nlist": "k_build_cells", "integrate": "k_kick"}
 
 
@@ -117,22 +117,23 @@ def flops_per_step(group, pc, k_corr=1):
         return (pc["A"] - pc["A_fe"]) * 1568 + (N - Nfe) * 1008
     if group == "bwd_radial":
         # per pair: geometry/basis+derivative 115, radial dg 18, record 20; Fe-Fe: 8 more
-        # channel values 144 + force/field terms 90; Fe-Ge: 36 + 30; per atom contractions
-        return pc["R"] * 153 + fe_centre_fe * 234 + fe_centre_ge * 66 + Nfe * 5 * 162 + N * 2 * 162
+        # channel values 144 + force/field terms 90; Fe-Ge: 36 + 30
+        return pc["R"] * 153 + fe_centre_fe * 234 + fe_centre_ge * 66
     if group == "couplings":
-        # per spin-step pass: per spin carrier the exchange, DMI and anisotropic
-        # contractions 486 and P = Fp^sa A 168; spin-angular part per Fe-Fe pair
-        # inside rc_A: geometry/basis 75, g^sa 126, harmonics 50, contraction 336 + 48
-        return (1 + k_corr) * (Nfe * (486 + 168) + pc["A_fefe"] * 635)
+        # per spin-step pass: per spin carrier P = Fp^sa A 168; spin-angular part per Fe-Fe
+        # pair inside rc_A: geometry/basis 75, g^sa 126, harmonics 50, contraction 336 + 48
+        return (1 + k_corr) * (Nfe * 168 + pc["A_fefe"] * 635)
     if group == "pairs":
         # per spin-step pass: per spin carrier the two single-ion contractions 324;
         # per Fe-Fe pair geometry/basis 80, three coupling values and the single-ion
         # weight 72, its tensor 21, rhat 33; per Fe-Ge pair 80 + 18 + 21
         return (1 + k_corr) * (Nfe * 324 + fe_centre_fe * (173 + 33) + fe_centre_ge * 119)
     if group == "readout":
-        # 2 x (104 x 64) FMA per atom + tanh, energy and gradient
+        # 2 x (104 x 64) FMA per atom + tanh, energy and gradient; the radial-set
+        # coefficients: two contractions per atom and five per spin carrier, in a
+        # spin-step pass the three magnetic ones
         per = 2 * 2 * 104 * 64 + 64 * 30
-        return N * per + (1 + k_corr) * Nfe * per
+        return N * (per + 2 * 162) + Nfe * 5 * 162 + (1 + k_corr) * Nfe * (per + 486)
     return None
 
 

@@ -346,13 +346,14 @@ int sl_destroy(sl_sim *s);
  * on the simulation's stream; totals accumulate until read. Groups:
  *   0 descriptor (radial set)   1 descriptor (angular set)   2 read-out
  *   3 backward (radial set)     4 backward (angular set), species 0
- *   5 gather                    6 spin-coupling coefficients and spin-angular parts
+ *   5 gather                    6 spin-angular parts of the spin couplings
  *   7 colour sweep              8 neighbour lists
  *   9 lattice half-steps, baths and reductions
  *  10 spin-pair coupling assembly
  *  11 backward (angular set), species 1
- * Systems of at most 65,536 atoms run groups 0 and 3 (but for the coefficients)
- * in the launches of groups 1 and 4, and group 11 in that of group 4.
+ * The read-out also forms the radial-set coefficients that groups 3 and 10 read.
+ * Systems of at most 65,536 atoms run groups 0 and 3 in the launches of groups 1
+ * and 4, and group 11 in that of group 4.
  * mask: bit g enables group g (0 disables timing). */
 #define SL_NPROF 12
 int sl_profile_enable(sl_sim *s, unsigned mask);

@@ -100,22 +100,6 @@ __device__ inline void contract(const real *c, const real *Fp, int nn, real C[NB
     }
 }
 
-// The same, with the atom's NR values read in one burst and the loop
-// unrolled: for the per-atom coefficient kernels, whose many resident waves
-// would otherwise evict an atom's row between the rolled loop's reads of it.
-template <typename real>
-__device__ inline void contract_burst(const real *c, const real *Fp, real C[NB]) {
-    real f[NR];
-#pragma unroll
-    for (int n = 0; n < NR; n++) f[n] = Fp[n];
-#pragma unroll
-    for (int k = 0; k < NB; k++) C[k] = 0;
-#pragma unroll
-    for (int n = 0; n < NR; n++)
-#pragma unroll
-        for (int k = 0; k < NB; k++) C[k] += f[n] * c[n * NB + k];
-}
-
 template <typename real>
 __device__ inline real dotk(const real C[NB], const real f[NB]) {
     real s = 0;
@@ -776,6 +760,13 @@ struct MF<float> {
 
 constexpr int MLP_WAVES = 8;           // 8 wavefronts x 16 atoms per workgroup
 constexpr int MLP_ATOMS = 16 * MLP_WAVES;
+// Launches of at most so many 16-atom tiles give a tile to four wavefronts
+// (SPLIT): a wavefront with a tile of its own runs 11,700 cycles of matrix
+// instructions in a row, and 512 atoms occupied two CUs. Per launch, FP64, the
+// former with its coefficient kernel: 512 atoms, full 22 + 13 -> 10 us, spin
+// pass 20 + 6 -> 8; 10,648 atoms 25 + 15 -> 23 and 21 + 7.5 -> 13. From about three
+// tiles per CU on the split form's staging of W0 for every tile costs as much.
+constexpr int MLP_SPLIT_TILES = 704;
 // LDS row stride of W0^T. The operand reads walk 16 rows (lanes i16) and 4
 // columns (lanes kq); a stride of 2 dwords mod 64 for 8-byte elements puts those
 // reads on distinct banks, and of 4 dwords for the 16-byte reads of FP32.
@@ -800,21 +791,82 @@ struct MlpLds<float> {
 // hidden tile. 2,097,152 atoms FP64, full pass 1.9 -> 1.43 ms, spin pass 0.95 ->
 // 0.61 (the products alone at the measured 71.8 TFLOP/s: 0.81 and 0.34);
 // 1,048,576 atoms FP32 0.60 -> 0.33 and 0.30 -> 0.155. With the descriptor rows
-// loaded beside W0 instead of after it: 1.36 and 0.58; 0.27 and 0.134.
-template <typename real, int KD, bool SPIN>
-__global__ void __launch_bounds__(512) k_mlp(Sys S, ModelDev<real> M, Work<real> W, int nbFe) {
+// loaded beside W0 instead of after it: 1.36 and 0.58; 0.27 and 0.134. With the
+// radial-set coefficients, formerly 0.54 and 0.22 (FP32 0.16 and 0.08) more: 1.53
+// and 0.66; 0.38 and 0.152.
+
+// The radial-set coefficients contracted with the atom's Fp, blocks b of NB
+// values: the radial channel's for each neighbour species p (b = p), CR_p[k] =
+// sum_n c^R_{2t+p}[n][k] Fp^R_n; on spin carriers the exchange, DMI and
+// anisotropic-exchange ones (b = 2, 3, 4; Fe-Fe pairs) and the single-ion ones
+// for each neighbour species (b = 5 + p), CS_p[k] = sum_n c^si_p[n][k] Fp^si_n.
+// rcoef holds [CR_0 | CR_1 | CS_0 | CS_1][N][NB]: a neighbour reads the NB values
+// of its own species (and NB more if it carries a spin), and atoms adjacent in
+// memory share cache lines; mcoef [N_fe][CE, CD, CA].
+// The accumulators of the second product are, element for element, the B
+// operands of this one, K_b Fp^T with a block's coefficients as a 16-row operand
+// from LDS, contracted over the block's entries of the descriptor alone: no
+// kernel reads Fp back for them.
+constexpr int COEF_BLOCKS = 7;
+constexpr int coef_entry(int b) { return b < 2 ? D_R : b == 2 ? D_EX : b == 3 ? D_DM : b == 4 ? D_AN : D_SI; }
+// does k-step r of descriptor tile x touch block b (over the lane quarters)?
+template <typename real>
+constexpr bool coef_step(int b, int x, int r) {
+    for (int kq = 0; kq < 4; kq++) {
+        const int n = 16 * x + (sizeof(real) == 8 ? kq + 4 * r : 4 * kq + r) - coef_entry(b);
+        if (n >= 0 && n < NR) return true;
+    }
+    return false;
+}
+// the steps of the blocks from b0 on, one after the other: the p-th, and the number of one
+struct CoefStep {
+    int b, x, r;
+};
+template <typename real>
+constexpr CoefStep coef_nth(int b0, int p) {
+    for (int b = b0; b < COEF_BLOCKS; b++)
+        for (int x = 0; x < (DP + 15) / 16; x++)
+            for (int r = 0; r < 4; r++)
+                if (coef_step<real>(b, x, r) && p-- == 0) return {b, x, r};
+    return {COEF_BLOCKS, 0, 0};
+}
+template <typename real>
+constexpr int coef_rank(int b0, int b, int x, int r) {
+    int p = 0;
+    for (CoefStep s = coef_nth<real>(b0, 0); s.b < b || (s.b == b && (s.x < x || (s.x == x && s.r < r)));)
+        s = coef_nth<real>(b0, ++p);
+    return p;
+}
+template <int... X>
+struct Tiles {
+    static constexpr int n = sizeof...(X);
+    static constexpr int at(int k) {
+        const int t[] = {X...};
+        return t[k];
+    }
+};
+
+// SPLIT: a workgroup of four wavefronts takes 16 atoms. Wavefront w forms hidden
+// units 16 w .. 16 w + 15, the activations meet in LDS, and each wavefront
+// takes the descriptor tiles of its coefficient blocks and its share of the
+// others. Every sum has the order of the other form, so the bits are the same.
+template <typename real, int KD, bool SPIN, bool SPLIT>
+__global__ void __launch_bounds__(SPLIT ? 256 : 512) k_mlp(Sys S, ModelDev<real> M, Work<real> W, int nbFe) {
     typedef typename MF<real>::acc_t acc_t;
-    constexpr int WLD = MlpLds<real>::LD;
+    constexpr int WLD = MlpLds<real>::LD, THREADS = SPLIT ? 256 : 512, ATOMS = SPLIT ? 16 : MLP_ATOMS;
     constexpr bool f64 = sizeof(real) == 8;
     constexpr int KDT = (KD + 15) / 16 * 16, NT = KDT / 16;
-    constexpr int T0 = SPIN ? D_OS / 16 : 0;   // first gradient tile
+    constexpr int B0 = SPIN ? 2 : 0, B1 = KD < DP ? 2 : SPIN ? 5 : COEF_BLOCKS;   // the pass's coefficient blocks
+    constexpr int NP = coef_rank<real>(B0, B1, 0, 0);
     __shared__ __align__(16) real sW[KDT * WLD];
     __shared__ real sB[2 * NH];   // b0, w1
+    __shared__ real sK[NP * 64];       // [step][lane]
+    __shared__ real sA[SPLIT ? 16 * 64 : 1];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const bool fe = (int)blockIdx.x < nbFe;
     const int t = fe ? 0 : 1;
     const int end = fe ? S.N_fe : S.N;
-    const int a0 = (fe ? blockIdx.x * MLP_ATOMS : S.N_fe + (blockIdx.x - nbFe) * MLP_ATOMS) + wave * 16;
+    const int a0 = (fe ? blockIdx.x * ATOMS : S.N_fe + (blockIdx.x - nbFe) * ATOMS) + (SPLIT ? 0 : wave * 16);
     const real *W0 = M.W0 + (size_t)t * DP * NH;
     // Every load of the kernel is issued here, before the first is used. The
     // rows of atoms that are not live are read too: an atom is a column of both
@@ -829,12 +881,12 @@ __global__ void __launch_bounds__(512) k_mlp(Sys S, ModelDev<real> M, Work<real>
         if constexpr (f64) return ks * 4 + kq;
         else return ks < KD / 16 * 4 ? (ks >> 2) * 16 + 4 * kq + (ks & 3) : KD / 16 * 16 + 2 * kq + (ks & 1);
     };
-    constexpr int SV = KDT * NH / (64 * MLP_WAVES);
-    static_assert(SV * 64 * MLP_WAVES == KDT * NH, "W0 is staged in whole rounds");
+    constexpr int SV = KDT * NH / THREADS;
+    static_assert(SV * THREADS == KDT * NH, "W0 is staged in whole rounds");
     real w0[SV];
 #pragma unroll
     for (int v = 0; v < SV; v++) {
-        const int x = v * 64 * MLP_WAVES + threadIdx.x;
+        const int x = v * THREADS + threadIdx.x;
         w0[v] = x < KD * NH ? W0[x] : real(0);
     }
     const real bw = threadIdx.x < NH ? M.b0[t * NH + threadIdx.x] : M.w1[t * NH + threadIdx.x % NH];
@@ -856,27 +908,58 @@ __global__ void __launch_bounds__(512) k_mlp(Sys S, ModelDev<real> M, Work<real>
         qa[KD / 4 - 2] = v.x;
         qa[KD / 4 - 1] = v.y;
     }
+    const bool mag = KD == DP && fe;   // the magnetic and single-ion blocks
+    static_for<NP>([&](auto PP) {
+        constexpr int p = decltype(PP)::value;
+        constexpr CoefStep c = coef_nth<real>(B0, p);
+        if (wave != p % (THREADS / 64)) return;
+        constexpr int first = coef_entry(c.b);
+        const int n = 16 * c.x + MF<real>::row(kq, c.r) - first;
+        const real *k = M.cR + (c.b < 2 ? P_CR + (2 * t + c.b) * NR * NB
+                                        : c.b == 2 ? P_CEX : c.b == 3 ? P_CDM : c.b == 4 ? P_CAN : P_CSI + (c.b - 5) * NR * NB);
+        sK[p * 64 + lane] = n >= 0 && n < NR && i16 < NB && (c.b < 2 || mag) ? k[n * NB + i16] : real(0);
+    });
     const bool rv = arow < end && rep.active;
     const real b1 = M.b1[t];
 #pragma unroll
     for (int v = 0; v < SV; v++) {
-        const int x = v * 64 * MLP_WAVES + threadIdx.x;
+        const int x = v * THREADS + threadIdx.x;
         sW[(x / NH) * WLD + x % NH] = w0[v];
     }
     if (threadIdx.x < 2 * NH) sB[threadIdx.x] = bw;
     __syncthreads();
     // Z^T = W0 Q^T + b0
-    acc_t z[4];
+    real act[4][4];
+    if constexpr (SPLIT) {
+        acc_t z;
 #pragma unroll
-    for (int mt = 0; mt < 4; mt++)
+        for (int r = 0; r < 4; r++) z[r] = sB[16 * wave + MF<real>::row(kq, r)];
 #pragma unroll
-        for (int r = 0; r < 4; r++) z[mt][r] = sB[16 * mt + MF<real>::row(kq, r)];
+        for (int ks = 0; ks < KD / 4; ks++) z = MF<real>::mma(sW[entry(ks) * WLD + wave * 16 + i16], qa[ks], z);
 #pragma unroll
-    for (int ks = 0; ks < KD / 4; ks++) {
+        for (int r = 0; r < 4; r++) sA[(4 * wave + r) * 64 + lane] = dtanh<real>(z[r]);
+        __syncthreads();
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++) z[mt] = MF<real>::mma(sW[entry(ks) * WLD + mt * 16 + i16], qa[ks], z[mt]);
+        for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) act[mt][r] = sA[(4 * mt + r) * 64 + lane];
+    } else {
+        acc_t z[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) z[mt][r] = sB[16 * mt + MF<real>::row(kq, r)];
+#pragma unroll
+        for (int ks = 0; ks < KD / 4; ks++) {
+#pragma unroll
+            for (int mt = 0; mt < 4; mt++) z[mt] = MF<real>::mma(sW[entry(ks) * WLD + mt * 16 + i16], qa[ks], z[mt]);
+        }
+#pragma unroll
+        for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) act[mt][r] = dtanh<real>(z[mt][r]);
     }
-    // activation, energy and the hidden-layer gradient
+    // energy and the hidden-layer gradient
     real e = 0;
     acc_t g[4];
 #pragma unroll
@@ -884,62 +967,140 @@ __global__ void __launch_bounds__(512) k_mlp(Sys S, ModelDev<real> M, Work<real>
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             const real w = sB[NH + 16 * mt + MF<real>::row(kq, r)];
-            const real a = dtanh<real>(z[mt][r]);
+            const real a = act[mt][r];
             e += w * a;
             g[mt][r] = w * (real(1) - a * a);
         }
-    if (!SPIN) {
+    if (!SPIN && (!SPLIT || wave == 0)) {
         e += __shfl_xor(e, 16);
         e += __shfl_xor(e, 32);
         if (kq == 0 && rv) W.Ei[arow] = b1 + e;
     }
-    // Fp^T = W0^T G^T: A = W0^T tile from LDS, B = this lane's g; the
-    // descriptor tiles in passes of at most four to bound the registers
+    // Fp^T = W0^T G^T: A = W0^T tile from LDS, B = this lane's g; at most four
+    // descriptor tiles at once to bound the registers
     real *fp = W.Fp + (size_t)(rv ? arow : 0) * DP;
-    constexpr int H0 = 4;
+    acc_t cb[COEF_BLOCKS];
 #pragma unroll
-    for (int d0 = T0; d0 < NT; d0 += H0) {
-        acc_t f[H0];
+    for (int b = 0; b < COEF_BLOCKS; b++) cb[b] = acc_t{0, 0, 0, 0};
+    // the tiles of TL, those whose bit is set in `stored` written out, and their
+    // part of the blocks [b0, b1)
+    const auto tiles = [&](auto TL, auto STORED, auto FIRST, auto LAST) {
+        typedef decltype(TL) T;
+        constexpr int stored = decltype(STORED)::value;
+        acc_t f[T::n];
 #pragma unroll
-        for (int x = 0; x < H0; x++) f[x] = acc_t{0, 0, 0, 0};
+        for (int x = 0; x < T::n; x++) f[x] = acc_t{0, 0, 0, 0};
 #pragma unroll
         for (int mt = 0; mt < 4; mt++) {
             if constexpr (f64) {
 #pragma unroll
                 for (int r = 0; r < 4; r++)
 #pragma unroll
-                    for (int x = 0; x < H0; x++)
-                        if (d0 + x < NT)
-                            f[x] = MF<real>::mma(sW[((d0 + x) * 16 + i16) * WLD + 16 * mt + 4 * r + kq], g[mt][r], f[x]);
+                    for (int x = 0; x < T::n; x++)
+                        f[x] = MF<real>::mma(sW[(T::at(x) * 16 + i16) * WLD + 16 * mt + 4 * r + kq], g[mt][r], f[x]);
             } else {
 #pragma unroll
-                for (int x = 0; x < H0; x++)
-                    if (d0 + x < NT) {
-                        const float4 w =
-                            *reinterpret_cast<const float4 *>(&sW[((d0 + x) * 16 + i16) * WLD + 16 * mt + 4 * kq]);
-                        f[x] = MF<real>::mma(w.x, g[mt][0], f[x]);
-                        f[x] = MF<real>::mma(w.y, g[mt][1], f[x]);
-                        f[x] = MF<real>::mma(w.z, g[mt][2], f[x]);
-                        f[x] = MF<real>::mma(w.w, g[mt][3], f[x]);
-                    }
+                for (int x = 0; x < T::n; x++) {
+                    const float4 w = *reinterpret_cast<const float4 *>(&sW[(T::at(x) * 16 + i16) * WLD + 16 * mt + 4 * kq]);
+                    f[x] = MF<real>::mma(w.x, g[mt][0], f[x]);
+                    f[x] = MF<real>::mma(w.y, g[mt][1], f[x]);
+                    f[x] = MF<real>::mma(w.z, g[mt][2], f[x]);
+                    f[x] = MF<real>::mma(w.w, g[mt][3], f[x]);
+                }
             }
         }
-        if (!rv) continue;
+        static_for<decltype(LAST)::value - decltype(FIRST)::value>([&](auto BB) {
+            constexpr int b = decltype(FIRST)::value + decltype(BB)::value;
+            static_for<T::n>([&](auto XX) {
+                constexpr int x = T::at(decltype(XX)::value);
+                static_for<4>([&](auto RR) {
+                    constexpr int r = decltype(RR)::value;
+                    if constexpr (coef_step<real>(b, x, r)) {
+                        constexpr int p = coef_rank<real>(B0, b, x, r);
+                        cb[b] = MF<real>::mma(sK[p * 64 + lane], f[decltype(XX)::value][r], cb[b]);
+                    }
+                });
+            });
+        });
+        if (!rv) return;
+        static_for<T::n>([&](auto XX) {
+            constexpr int k = decltype(XX)::value, x = T::at(k);
+            if constexpr ((stored >> k & 1) != 0) {
+                if constexpr (f64) {
 #pragma unroll
-        for (int x = 0; x < H0; x++) {
-            if (d0 + x >= NT) continue;
-            if constexpr (f64) {
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int d = (d0 + x) * 16 + kq + 4 * r;
-                    if (d < KD) fp[d] = f[x][r];
+                    for (int r = 0; r < 4; r++) {
+                        const int d = x * 16 + kq + 4 * r;
+                        if (d < KD) fp[d] = f[k][r];
+                    }
+                } else {
+                    const int d = x * 16 + 4 * kq;   // KD is a multiple of four
+                    if (d < KD) *reinterpret_cast<float4 *>(fp + d) = make_float4(f[k][0], f[k][1], f[k][2], f[k][3]);
                 }
+            }
+        });
+    };
+    const auto put = [&](auto FIRST, auto LAST) {
+        if (!rv) return;
+        static_for<decltype(LAST)::value - decltype(FIRST)::value>([&](auto BB) {
+            constexpr int b = decltype(FIRST)::value + decltype(BB)::value;
+            if (b >= 2 && !mag) return;
+            real *o = b >= 2 && b < 5 ? W.mcoef + (size_t)arow * MCOEF + (b - 2) * NB
+                                      : W.rcoef + ((size_t)(b < 2 ? b : b - 3) * S.N + arow) * NB;
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int k = MF<real>::row(kq, r);
+                if (k < NB) o[k] = cb[b][r];
+            }
+        });
+    };
+#define I_(x) std::integral_constant<int, x>{}
+    if constexpr (!SPLIT) {
+        if constexpr (KD < DP) {
+            tiles(Tiles<0, 1, 2>{}, I_(7), I_(0), I_(2));
+            put(I_(0), I_(2));
+        } else if constexpr (SPIN) {
+            tiles(Tiles<2, 3, 4>{}, I_(7), I_(2), I_(5));
+            put(I_(2), I_(5));
+            tiles(Tiles<5, 6>{}, I_(3), I_(0), I_(0));
+        } else {
+            tiles(Tiles<0, 1, 2>{}, I_(7), I_(0), I_(4));   // block 3 starts in tile 2
+            put(I_(0), I_(3));
+            tiles(Tiles<3, 4, 5, 6>{}, I_(15), I_(3), I_(7));
+            put(I_(3), I_(7));
+        }
+    } else if constexpr (KD < DP) {
+        if (wave == 0) {
+            tiles(Tiles<0>{}, I_(1), I_(0), I_(2));
+            put(I_(0), I_(2));
+        } else if (wave == 1) {
+            tiles(Tiles<1>{}, I_(1), I_(0), I_(0));
+        } else if (wave == 2) {
+            tiles(Tiles<2>{}, I_(1), I_(0), I_(0));
+        }
+    } else {
+        if (wave == 0) {
+            if constexpr (SPIN) {
+                tiles(Tiles<6>{}, I_(1), I_(0), I_(0));
             } else {
-                const int d = (d0 + x) * 16 + 4 * kq;   // KD is a multiple of four
-                if (d < KD) *reinterpret_cast<float4 *>(fp + d) = make_float4(f[x][0], f[x][1], f[x][2], f[x][3]);
+                tiles(Tiles<0, 1, 6>{}, I_(7), I_(0), I_(2));
+                put(I_(0), I_(2));
+            }
+        } else if (wave == 1) {
+            tiles(Tiles<2, 3>{}, I_(3), I_(2), I_(4));
+            put(I_(2), I_(4));
+        } else if (wave == 2) {
+            tiles(Tiles<3, 4>{}, I_(2), I_(4), I_(5));
+            put(I_(4), I_(5));
+        } else {
+            if constexpr (SPIN) {
+                tiles(Tiles<5>{}, I_(1), I_(0), I_(0));
+            } else {
+                tiles(Tiles<4, 5>{}, I_(2), I_(5), I_(7));
+                put(I_(5), I_(7));
             }
         }
     }
+#undef I_
 }
 
 // -------------------------------------------------------------------------
@@ -955,62 +1116,6 @@ __device__ inline void put_pair(real *pb, size_t idx, const real G[3], const rea
     p[3] = h[0];
     p[4] = h[1];
     p[5] = h[2];
-}
-
-// Per atom i of species t, its radial-set coefficients contracted with its
-// own Fp, for each neighbour species p: CR_p[k] = sum_n c^R_{2t+p}[n][k] Fp^R_n
-// and, on spin carriers, CS_p[k] = sum_n c^si_{2t+p}[n][k] Fp^si_n (zero on
-// the others). Stored as [CR_0 | CR_1 | CS_0 | CS_1][N][NB]: a neighbour reads
-// the NB values of its own species (and NB more if it carries a spin), and
-// atoms adjacent in memory share cache lines. Spin carriers also get the exchange, DMI and
-// anisotropic-exchange coefficients (Fe-Fe pairs), [N_fe][CE, CD, CA].
-template <typename real>
-__device__ inline void mag_coef(const real *__restrict__ C, const real *Fp, real *m) {
-    real CX[NB];
-    contract_burst((C + P_CEX), Fp + D_EX, CX);
-#pragma unroll
-    for (int k = 0; k < NB; k++) m[k] = CX[k];
-    contract_burst((C + P_CDM), Fp + D_DM, CX);
-#pragma unroll
-    for (int k = 0; k < NB; k++) m[NB + k] = CX[k];
-    contract_burst((C + P_CAN), Fp + D_AN, CX);
-#pragma unroll
-    for (int k = 0; k < NB; k++) m[2 * NB + k] = CX[k];
-}
-
-template <typename real>
-__global__ void __launch_bounds__(256) k_radial_coef(Sys S, const real *__restrict__ C, Work<real> W) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= S.N || live(S, i) < 0) return;
-    const bool fe = i < S.N_fe;
-    const int t = fe ? 0 : 1;
-    const real *Fp = W.Fp + (size_t)i * DP;
-    const size_t ld = S.N;
-#pragma unroll 1
-    for (int p = 0; p < 2; p++) {
-        real CR[NB];
-        contract_burst((C + P_CR) + (2 * t + p) * NR * NB, Fp + D_R, CR);
-        real *oR = W.rcoef + ((size_t)p * ld + i) * NB;
-#pragma unroll
-        for (int k = 0; k < NB; k++) oR[k] = CR[k];
-        if (fe && S.mag) {   // single-ion block, read only for spin-carrying partners
-            real CS[NB];
-            contract_burst((C + P_CSI) + p * NR * NB, Fp + D_SI, CS);
-            real *oS = W.rcoef + ((size_t)(2 + p) * ld + i) * NB;
-#pragma unroll
-            for (int k = 0; k < NB; k++) oS[k] = CS[k];
-        }
-    }
-    if (fe && S.mag) mag_coef(C, Fp, W.mcoef + (size_t)i * MCOEF);
-}
-
-// the exchange, DMI and anisotropic-exchange coefficients alone, spin carriers
-// (the spin-step passes)
-template <typename real>
-__global__ void __launch_bounds__(256) k_mag_coef(Sys S, const real *__restrict__ C, Work<real> W) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= S.N_fe || live(S, i) < 0) return;
-    mag_coef(C, W.Fp + (size_t)i * DP, W.mcoef + (size_t)i * MCOEF);
 }
 
 // Structural part of the radial-set backward pass: the radial channel of
@@ -1843,20 +1948,28 @@ void launch_desc_angular(const Sys &S, const ModelDev<real> &M, const Work<real>
 template <typename real>
 void launch_mlp(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int mode, hipStream_t st) {
     if (S.N == 0) return;
+    const int t_fe = nblk(S.N_fe, 16), tiles = mode == PASS_FULL ? t_fe + nblk(S.N - S.N_fe, 16) : t_fe;
+    if (!tiles) return;
+    if (tiles <= MLP_SPLIT_TILES) {
+        const int nb_fe = t_fe;
+        const dim3 g(tiles), b(256);
+        if (!S.mag) hipLaunchKernelGGL((k_mlp<real, DS_PAD, false, true>), g, b, 0, st, S, M, W, nb_fe);
+        else if (mode == PASS_FULL) hipLaunchKernelGGL((k_mlp<real, DP, false, true>), g, b, 0, st, S, M, W, nb_fe);
+        else hipLaunchKernelGGL((k_mlp<real, DP, true, true>), g, b, 0, st, S, M, W, nb_fe);
+        return;
+    }
     NEP_SPLIT(MLP_ATOMS)
     const int nb = mode == PASS_FULL ? nb_fe + nb_ge : nb_fe;
-    if (!nb) return;
     const dim3 g(nb), b(64 * MLP_WAVES);
-    if (!S.mag) hipLaunchKernelGGL((k_mlp<real, DS_PAD, false>), g, b, 0, st, S, M, W, nb_fe);
-    else if (mode == PASS_FULL) hipLaunchKernelGGL((k_mlp<real, DP, false>), g, b, 0, st, S, M, W, nb_fe);
-    else hipLaunchKernelGGL((k_mlp<real, DP, true>), g, b, 0, st, S, M, W, nb_fe);
+    if (!S.mag) hipLaunchKernelGGL((k_mlp<real, DS_PAD, false, false>), g, b, 0, st, S, M, W, nb_fe);
+    else if (mode == PASS_FULL) hipLaunchKernelGGL((k_mlp<real, DP, false, false>), g, b, 0, st, S, M, W, nb_fe);
+    else hipLaunchKernelGGL((k_mlp<real, DP, true, false>), g, b, 0, st, S, M, W, nb_fe);
 }
 
 template <typename real>
 void launch_bwd_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &W, hipStream_t st) {
     if (S.N == 0) return;
     NEP_SPLIT(256)
-    hipLaunchKernelGGL(k_radial_coef<real>, dim3(nblk(S.N, 256)), dim3(256), 0, st, S, M.cR, W);
     if (!S.narrow) return;
     hipLaunchKernelGGL(k_bwd_radial<real>, dim3(nb_fe + nb_ge), dim3(256), 0, st, S, M.cR, W, nb_fe);
     if (nb_fe && S.mag) hipLaunchKernelGGL(k_bwd_mag<real>, dim3(nb_fe), dim3(256), 0, st, S, W);
@@ -1899,7 +2012,6 @@ void launch_gather(const Sys &S, const Work<real> &W, hipStream_t st) {
 template <typename real>
 void launch_assemble_coef(const Sys &S, const ModelDev<real> &M, const Work<real> &W, hipStream_t st) {
     if (S.N_fe == 0) return;
-    hipLaunchKernelGGL(k_mag_coef<real>, dim3(nblk(S.N_fe, 256)), dim3(256), 0, st, S, M.cR, W);
     hipLaunchKernelGGL(k_assemble_angular<real>, dim3(nblk(S.N_fe, ANG_ATOMS)), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W);
 }
 
