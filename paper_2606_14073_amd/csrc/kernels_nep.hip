@@ -2,16 +2,19 @@
 // read-out, backward pass (forces and effective fields) and the bilinear spin
 // couplings of the frozen-Fp magnetic energy.
 //
-// Mapping. Radial-set work (radial, exchange, DMI, anisotropic, single-ion
-// channels over the 6 A list) runs one lane per atom. Angular-set work
-// (angular and spin-angular channels over the 4.5 A list) runs eight lanes
-// per atom, lane n owning the 24 harmonic accumulators A_nlm and B_nlm of
-// radial function n. Spin-carrying atoms occupy the leading index range and
-// every grid is split so that a wavefront never mixes species; neighbour
-// rows list spin carriers first, so the pair type tau, and with it every
-// coefficient address, is uniform across the wavefront inside each loop.
-// Sums over neighbours run in list order (ascending atom index): results are
-// deterministic and independent of how replicas are batched.
+// Mapping. Every kernel walks lists of the neighbours inside the cutoffs, put
+// together from the Verlet rows by k_active for each new set of positions.
+// Radial-set work (radial, exchange, DMI, anisotropic, single-ion channels
+// inside 6 A) runs one lane per atom, or eight in small replicas. Angular-set
+// work (angular and spin-angular channels inside 4.5 A) takes eight atoms per
+// wavefront: the descriptor eight lanes per atom, each with a tile of the
+// accumulators A_nlm and B_nlm, the backward pass and the coupling assembly a
+// lane per pair. Spin-carrying atoms occupy the leading index range and every grid
+// is split so that a wavefront never mixes species; the lists hold spin
+// carriers first, so the pair type tau, and with it every coefficient address,
+// is uniform across the wavefront inside each loop. Sums over neighbours follow
+// the in-cutoff ranks (ascending atom index): results are deterministic and
+// independent of how replicas are batched.
 //
 // Gather without atomics: the backward pass writes, per listed pair (i,j),
 // dE_i/dd_ij and dE_i/ds_j into a pair record; a gather kernel then forms
@@ -166,32 +169,52 @@ struct CutTest {
 
 // The lists are put together in LDS and written in whole lines: stored by each
 // lane as it went along (its ranks differ from its neighbours') they left L2 in
-// parts, 3.8 times their bytes.
+// parts, 3.8 times their bytes. Latency bounds it, so LDS holds the ranks that a
+// crystal or a liquid has (62 and 29 in FeGe, about 90 and 38 in water) and any
+// further ones are stored one by one: six workgroups fit in a CU's LDS instead
+// of three; and the partner's slot is used a round after its load. Mean of a
+// step's two passes: 2,097,152 atoms 1.06 -> 0.75 ms; 1,048,576 in a slab, FP32
+// 0.52 -> 0.37; 262,144 128 -> 87 us; 375,000 water atoms 304 -> 205 (one pass).
+constexpr int ACT_R = 96, ACT_A = 48;
 template <typename real>
 __global__ void __launch_bounds__(256) k_active(Sys S, int n) {
     constexpr int ATOMS = 32;
-    __shared__ int sR[MAXR * ATOMS];                        // [rank][atom]
-    __shared__ __align__(16) int sA[ATOMS * MAXA];          // [atom][rank]
-    __shared__ __align__(8) uint16_t sS[ATOMS * MAXA];
+    __shared__ int sR[ACT_R * ATOMS];                       // [rank][atom]
+    __shared__ __align__(16) int sA[ATOMS * ACT_A];         // [atom][rank]
+    __shared__ __align__(8) uint16_t sS[ATOMS * ACT_A];
     __shared__ uint16_t sX[MAXFE * ATOMS];                  // [rank][atom]
     __shared__ int sn[2 * ATOMS];                           // entries of sR and sX
     const int lane = threadIdx.x & 7, gbase = threadIdx.x & 56, at = threadIdx.x >> 3;
     const int first = blockIdx.x * ATOMS;
-    const int i = live(S, first + at < n ? first + at : -1);
     const size_t ld = S.N, lf = S.N_fe;
     int nR = 0, nA = 0, nX = 0;
+    // the loads of the prologue together; the first two row entries are read
+    // before the row's length is known, and bounded in case they lie beyond it
+    const int ii = min(first + at, n - 1);
+    const RepDev &rep = S.rep[S.rid[ii]];
+    const int len = S.lenR[ii], lenfe = S.lenFeR[ii];
+    const d4 pi = S.pos[ii];
+    int vn = S.rowR[(size_t)lane * ld + ii], vm = S.rowR[(size_t)(lane + 8) * ld + ii];
+    if ((vn & ~ANG_BIT) >= S.N) vn = ii;
+    float4 qn = S.pos4[vn & ~ANG_BIT];
+    const int i = first + at < n && rep.active ? ii : -1;
     if (i >= 0) {
-        const Img R = img_of(S.rep[S.rid[i]]);
+        const Img R = img_of(rep);
         CutTest<real> cut;
-        cut.set(R, S.pos[i]);
-        const int len = S.lenR[i], lenfe = S.lenFeR[i];
+        cut.set(R, pi);
         const int mx = S.mag && i < S.N_fe ? MAXFE : 0;
         const unsigned below = (1u << lane) - 1u;
         int nL = 0, nFeR = 0, nFeA = 0;
-        // the row entry two rounds ahead, its position one round ahead
-        int vn = lane < len ? S.rowR[(size_t)lane * ld + i] : i;
-        int vm = lane + 8 < len ? S.rowR[(size_t)(lane + 8) * ld + i] : i;
-        float4 qn = S.pos4[vn & ~ANG_BIT];
+        // the row entry two rounds ahead, its position one round ahead; the
+        // partner's slot is used one round after its load was started
+        if (lane + 8 >= len) vm = i;
+        int po = -1, px = -1, pa = 0, prev = 0;   // the pair's angular rank, its place in sX, and its slots
+        const auto put_slots = [&]() {
+            const uint16_t sr = (uint16_t)(pa | prev << 8);
+            if (po >= ACT_A) S.actS[(size_t)i * MAXA + po] = sr;
+            else if (po >= 0) sS[at * ACT_A + po] = sr;
+            if (px >= 0) sX[px] = po >= 0 ? sr : 0;
+        };
         for (int s0 = 0; s0 < len; s0 += 8) {
             const int s = s0 + lane, v = vn, j = v & ~ANG_BIT;
             const float4 q = qn;
@@ -206,16 +229,19 @@ __global__ void __launch_bounds__(256) k_active(Sys S, int n) {
             const unsigned mR = (unsigned)(__ballot(in) >> gbase) & 0xffu;
             const unsigned mA = (unsigned)(__ballot(inA) >> gbase) & 0xffu;
             const int kR = nR + __popc(mR & below);
-            int sr = 0;
+            put_slots();
+            po = px = -1;
             if (inA) {
-                const int a = nL + __popc(mL & below), o = at * MAXA + nA + __popc(mA & below);
-                sr = a | (int)S.revA[(size_t)a * ld + i] << 8;
-                sA[o] = j;
-                sS[o] = (uint16_t)sr;
+                pa = nL + __popc(mL & below);
+                po = nA + __popc(mA & below);
+                prev = S.revA[(size_t)pa * ld + i];
+                if (po < ACT_A) sA[at * ACT_A + po] = j;
+                else S.actA[(size_t)i * MAXA + po] = j;
             }
             if (in) {
-                sR[kR * ATOMS + at] = j;
-                if (s < lenfe && kR < mx) sX[kR * ATOMS + at] = (uint16_t)sr;
+                if (kR < ACT_R) sR[kR * ATOMS + at] = j;
+                else S.actR[(size_t)kR * ld + i] = j;
+                if (s < lenfe && kR < mx) px = kR * ATOMS + at;
             }
             nL += __popc(mL);
             nR += __popc(mR);
@@ -226,6 +252,7 @@ __global__ void __launch_bounds__(256) k_active(Sys S, int n) {
                 nFeA += __popc(mA & mf);
             }
         }
+        put_slots();
         nX = min(nFeR, mx);
         if (lane == 0) {
             S.cntR[i] = nR;
@@ -235,17 +262,17 @@ __global__ void __launch_bounds__(256) k_active(Sys S, int n) {
         }
     }
     if (lane == 0) {
-        sn[at] = nR;
+        sn[at] = min(nR, ACT_R);
         sn[ATOMS + at] = nX;
     }
     __syncthreads();
     const int a2 = threadIdx.x & (ATOMS - 1), r0 = threadIdx.x / ATOMS;
     for (int r = r0; r < sn[a2]; r += 256 / ATOMS) S.actR[(size_t)r * ld + first + a2] = sR[r * ATOMS + a2];
     for (int r = r0; r < sn[ATOMS + a2]; r += 256 / ATOMS) S.xS[(size_t)r * lf + first + a2] = sX[r * ATOMS + a2];
-    for (int k = 4 * lane; k < nA; k += 32) {
-        *reinterpret_cast<int4 *>(S.actA + (size_t)i * MAXA + k) = *reinterpret_cast<const int4 *>(sA + at * MAXA + k);
+    for (int k = 4 * lane; k < min(nA, ACT_A); k += 32) {
+        *reinterpret_cast<int4 *>(S.actA + (size_t)i * MAXA + k) = *reinterpret_cast<const int4 *>(sA + at * ACT_A + k);
         *reinterpret_cast<ushort4 *>(S.actS + (size_t)i * MAXA + k) =
-            *reinterpret_cast<const ushort4 *>(sS + at * MAXA + k);
+            *reinterpret_cast<const ushort4 *>(sS + at * ACT_A + k);
     }
 }
 
@@ -1104,7 +1131,7 @@ __global__ void __launch_bounds__(SPLIT ? 256 : 512) k_mlp(Sys S, ModelDev<real>
 }
 
 // -------------------------------------------------------------------------
-// backward: radial set (lane per atom)
+// backward: radial set
 // -------------------------------------------------------------------------
 
 template <typename real>
@@ -1119,7 +1146,7 @@ __device__ inline void put_pair(real *pb, size_t idx, const real G[3], const rea
 }
 
 // Structural part of the radial-set backward pass: the radial channel of
-// every pair and the single-ion term of spin-carrying centres, lane per atom.
+// every pair and the single-ion term of spin-carrying centres, L lanes per atom.
 // Both halves of each pair come from this lane: G_ij = dE_i/dd_ij from the
 // atom's own coefficients and G_ji = dE_j/dd_ji from the neighbour's
 // contracted block (and its spin), so F_i = sum_j (G_ij - G_ji) needs no
@@ -1311,7 +1338,7 @@ __global__ void __launch_bounds__(256) k_bwd_radial(Sys S, const real *__restric
 
 // Magnetic pair part of the radial-set backward pass: exchange, DMI and
 // anisotropic exchange over the spin-carrying neighbours of spin-carrying
-// centres, lane per atom. The partner's pair energy e_ji has the form of e_ij
+// centres, L lanes per atom. The partner's pair energy e_ji has the form of e_ij
 // in terms of d_ij (r_hat_ji.(s_j x s_i) = r_hat_ij.(s_i x s_j), and likewise
 // for the anisotropic product), so a pair's force on i and field on s_i are
 // the formulas of e_ij with the summed coefficients C_i + C_j: no records.
@@ -1786,9 +1813,9 @@ __global__ void __launch_bounds__(64) k_assemble_angular(Sys S, const real *__re
 // D_ij = d_ij + d_ji, K_ij = b_ij + b_ji: the radial-set parts are sums over
 // the basis with the summed contracted coefficients of both spins, the
 // spin-angular parts (inside rc_A) the two atoms' records. Stored with rhat_ij
-// compactly in list order, so the sweep's split of a spin's couplings over
-// lanes depends on the positions alone and not on which farther atoms the
-// Verlet list happens to hold. The same pass sums the single-ion tensor
+// by in-cutoff rank, so the sweep's split of a spin's couplings over lanes
+// depends on the positions alone and not on which farther atoms the Verlet list
+// happens to hold. The same pass sums the single-ion tensor
 // A_i = sum_j g^si(r_ij) rhat rhat^T over all neighbours.
 template <typename real, int L>
 __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__restrict__ C, Work<real> W) {

@@ -28,6 +28,7 @@ def cluster(n, spacing, seed, offset):
 
 @pytest.mark.parametrize("n,spacing,offset", [
     (1, 2.5, 0.0), (2, 2.5, 0.0), (8, 2.5, 0.0), (31, 2.5, 0.0), (32, 2.5, 1.0e3), (33, 2.5, 0.0), (65, 2.2, 0.0),
+    (125, 1.9, 0.0),            # more ranks inside the cutoffs than the lists are put together for
     (343, 2.0, 0.0),            # lists near the longest allowed, several rounds of 64 pairs
     (216, 2.5, 1.0e5),          # single-precision coordinates 0.008 A apart
 ])
