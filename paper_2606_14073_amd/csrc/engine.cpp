@@ -311,13 +311,35 @@ struct Engine {
 
     ~Engine() { release(); }
 
+    // the neighbour lists of c atoms, cf of them spin carriers
+    int get_lists(size_t c, size_t cf) {
+        int rc;
+        if ((rc = get(&rowR, (size_t)MAXR * c)) || (rc = get(&actR, (size_t)MAXR * c)) ||
+            (rc = get(&actA, (size_t)MAXA * c)) || (rc = get(&actS, (size_t)MAXA * c + (size_t)MAXFE * cf)) ||
+            (rc = get(&r2a, (size_t)(MAXR + MAXA) * c)) || (rc = get(&lenR, 6 * c)) || (rc = get(&pos4, c)))
+            return rc;
+        xS = actS + (size_t)MAXA * c;
+        revA = r2a + (size_t)MAXR * c;
+        lenFeR = lenR + c;
+        cntR = lenR + 2 * c;
+        cntFeR = lenR + 3 * c;
+        cntA = lenR + 4 * c;
+        cntFeA = lenR + 5 * c;
+        return SL_OK;
+    }
+    void put_lists() {
+        put(rowR); put(actR); put(actA); put(actS); put(r2a); put(lenR); put(pos4);
+        xS = nullptr;
+        revA = nullptr;
+        lenFeR = cntR = cntFeR = cntA = cntFeA = nullptr;
+    }
+
     void release() {
         put(rid); put(orig); put(colour); put(rep);
         put(pos); put(vel); put(spin); put(force); put(field); put(pos_ref);
         put(spin_n); put(spin_hat); put(eta);
         put(sc_x); put(sc_f); put(sc_g); put(sc_dF); put(sc_dG); put(sc_part); put(sc_out);
-        put(rowR); put(lenR); put(lenFeR); put(r2a); put(revA);
-        put(actR); put(cntR); put(cntFeR); put(actA); put(cntA); put(cntFeA); put(actS); put(xS); put(pos4);
+        put_lists();
         put(cell_of); put(cell_cnt); put(cell_start); put(cell_fill); put(cell_atoms);
         put(flags); put(chunks); put(chunk_ptr); put(col_idx); put(colpos); put(col_rid); put(cpl_j); put(cpl_n);
         put(partial); put(obs); put(act_buf);
@@ -418,8 +440,7 @@ struct Engine {
             put(pos); put(vel); put(spin); put(force); put(field); put(pos_ref);
             put(spin_n); put(spin_hat); put(eta);
             put(sc_x); put(sc_f); put(sc_g); put(sc_dF); put(sc_dG); put(sc_part);
-            put(rowR); put(lenR); put(lenFeR); put(r2a); put(revA);
-            put(actR); put(cntR); put(cntFeR); put(actA); put(cntA); put(cntFeA); put(actS); put(xS); put(pos4);
+            put_lists();
             put(cell_of); put(cell_atoms); put(cpl_j); put(cpl_n);
             if (work && !arena) (void)hipFree(work);
             work = nullptr;
@@ -428,12 +449,7 @@ struct Engine {
                 (rc = get(&pos, c)) || (rc = get(&vel, c)) || (rc = get(&spin, c)) ||
                 (rc = get(&force, c)) || (rc = get(&field, c)) || (rc = get(&pos_ref, c)) ||
                 (rc = get(&spin_n, c)) || (rc = get(&spin_hat, c)) || (rc = get(&eta, c)) ||
-                (rc = get(&rowR, (size_t)MAXR * c)) || (rc = get(&lenR, c)) || (rc = get(&lenFeR, c)) ||
-                (rc = get(&actR, (size_t)MAXR * c)) || (rc = get(&cntR, c)) || (rc = get(&cntFeR, c)) ||
-                (rc = get(&xS, (size_t)MAXFE * cf)) || (rc = get(&pos4, c)) ||
-                (rc = get(&r2a, (size_t)MAXR * c)) || (rc = get(&revA, (size_t)MAXA * c)) ||
-                (rc = get(&actA, (size_t)MAXA * c)) || (rc = get(&actS, (size_t)MAXA * c)) ||
-                (rc = get(&cntA, c)) || (rc = get(&cntFeA, c)) || (rc = get(&cell_of, c)) ||
+                (rc = get_lists(c, cf)) || (rc = get(&cell_of, c)) ||
                 (rc = get(&cell_atoms, c)) || (rc = get(&cpl_j, (size_t)MAXFE * cf)) ||
                 (rc = get(&cpl_n, cf)) || (rc = get(&sc_x, cf)))
                 return rc;
