@@ -70,7 +70,7 @@ struct Sys {
     int *actR, *cntR, *cntFeR;
     int *actA, *cntA, *cntFeA;
     uint16_t *actS, *xS;
-    float4 *pos4;          // positions in single precision, for the cutoff tests that are not close
+    float4 *pos4;          // positions folded into the box, in single precision, for the cutoff tests that are not close
     int *cell_of, *cell_cnt, *cell_start, *cell_fill, *cell_atoms;
     int *flags;
 };
@@ -146,7 +146,7 @@ void launch_sweep(const Sys &S, const Work<real> &W, const int *col_ptr_host, in
 
 void launch_kick(const Sys &S, hipStream_t st);
 void launch_drift(const Sys &S, hipStream_t st);   // also refreshes pos4
-void launch_pos4(const Sys &S, hipStream_t st);    // pos4 from pos
+void launch_pos4(const Sys &S, hipStream_t st);    // pos4 from pos, given in any image
 void launch_langevin(const Sys &S, hipStream_t st);
 void launch_spin_prep(const Sys &S, hipStream_t st);
 void launch_spin_restore(const Sys &S, hipStream_t st);

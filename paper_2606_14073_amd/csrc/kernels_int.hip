@@ -24,6 +24,24 @@ __global__ void k_kick(Sys S) {
     S.vel[i] = v;
 }
 
+// The single-precision copy of a position, for the cutoff tests that are not
+// close: their error bound takes periodic coordinates to lie in the box, and
+// folding them to cost no more than rounding. A coordinate for which that does
+// not hold becomes NaN, which leaves its tests undecided.
+constexpr double FOLD_MAX = 1.0e7;   // A; beyond it a coordinate's own rounding (1e-9 A) enters the bound
+__device__ inline float fold4(const RepDev &R, int a, double x) {
+    return !R.pbc[a] || (x >= -1.0 && x <= R.box[a] + 1.0) ? (float)x : __int_as_float(0x7fc00000);
+}
+__device__ inline float4 pos4_of(const RepDev &R, const d4 &p) {
+    return make_float4(fold4(R, 0, p.x), fold4(R, 1, p.y), fold4(R, 2, p.z), 0.0f);
+}
+
+__device__ inline void fold(const RepDev &R, d4 &p) {
+    if (R.pbc[0]) p.x -= R.box[0] * floor(p.x / R.box[0]);
+    if (R.pbc[1]) p.y -= R.box[1] * floor(p.y / R.box[1]);
+    if (R.pbc[2]) p.z -= R.box[2] * floor(p.z / R.box[2]);
+}
+
 __global__ void k_drift(Sys S) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= S.N) return;
@@ -35,18 +53,21 @@ __global__ void k_drift(Sys S) {
     p.x += h * v.x;
     p.y += h * v.y;
     p.z += h * v.z;
-    if (R.pbc[0]) p.x -= R.box[0] * floor(p.x / R.box[0]);
-    if (R.pbc[1]) p.y -= R.box[1] * floor(p.y / R.box[1]);
-    if (R.pbc[2]) p.z -= R.box[2] * floor(p.z / R.box[2]);
+    fold(R, p);
     S.pos[i] = p;
-    S.pos4[i] = make_float4((float)p.x, (float)p.y, (float)p.z, 0.0f);
+    S.pos4[i] = pos4_of(R, p);
 }
 
 __global__ void k_pos4(Sys S) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= S.N) return;
-    const d4 p = S.pos[i];
-    S.pos4[i] = make_float4((float)p.x, (float)p.y, (float)p.z, 0.0f);
+    const RepDev &R = S.rep[S.rid[i]];
+    d4 p = S.pos[i];   // the caller's, in any image
+    const bool far = fmax(fabs(p.x), fmax(fabs(p.y), fabs(p.z))) > FOLD_MAX && (R.pbc[0] || R.pbc[1] || R.pbc[2]);
+    fold(R, p);
+    float4 q = pos4_of(R, p);
+    if (far) q.x = __int_as_float(0x7fc00000);
+    S.pos4[i] = q;
 }
 
 __device__ inline double temperature(const RepDev &R) { return R.T0 + (R.T1 - R.T0) * ramp_frac(R); }

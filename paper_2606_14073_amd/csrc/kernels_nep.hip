@@ -132,14 +132,15 @@ template <typename real>
 struct CutTest {
     static constexpr real rc = (real)RC_R, rca = (real)RC_A;
     float px, py, pz, bx, by, bz, ix, iy, iz, tol;
-    __device__ void set(const Img &R, const d4 &pi) {
-        px = (float)pi.x, py = (float)pi.y, pz = (float)pi.z;
+    __device__ void set(const Img &R, const float4 &p) {
+        px = p.x, py = p.y, pz = p.z;
         bx = (float)R.b[0], by = (float)R.b[1], bz = (float)R.b[2];
         ix = (float)R.ib[0], iy = (float)R.ib[1], iz = (float)R.ib[2];
-        // Rounding of r^2 near a cutoff: coordinates, box edge and differences
-        // are at most M, each rounded by 2^-24 M or less, five of them per
-        // component; r below 7 A, so 2 sqrt(3) r e + 3 e^2 for the components
-        // and 1e-5 for the sum.
+        // Rounding of r^2 near a cutoff: with periodic coordinates folded into
+        // the box (pos4), both atoms' coordinates, the box edge, its multiple
+        // (0 or +-1 edges) and the differences are at most M, each rounded by
+        // 2^-24 M or less, five of them per component; r below 7 A, so
+        // 2 sqrt(3) r e + 3 e^2 for the components and 1e-5 for the sum.
         float M = fmaxf(fmaxf(fabsf(px), fabsf(py)), fabsf(pz));
         M = fmaxf(M, fmaxf(fmaxf(bx, by), bz)) + 7.0f;
         const float e = M * 3.0e-7f;
@@ -158,7 +159,7 @@ struct CutTest {
         const float f2 = r2(q);
         in = f2 < c2;
         inA = f2 < ca2;
-        if (fabsf(f2 - c2) < tol || fabsf(f2 - ca2) < tol) {
+        if (!(fabsf(f2 - c2) >= tol && fabsf(f2 - ca2) >= tol)) {   // also for NaN
             real d[3];
             const real x2 = geom_p(R, S.pos[i], S.pos[j], d);
             in = x2 < rc * rc;
@@ -193,7 +194,7 @@ __global__ void __launch_bounds__(256) k_active(Sys S, int n) {
     const int ii = min(first + at, n - 1);
     const RepDev &rep = S.rep[S.rid[ii]];
     const int len = S.lenR[ii], lenfe = S.lenFeR[ii];
-    const d4 pi = S.pos[ii];
+    const float4 pi = S.pos4[ii];
     int vn = S.rowR[(size_t)lane * ld + ii], vm = S.rowR[(size_t)(lane + 8) * ld + ii];
     if ((vn & ~ANG_BIT) >= S.N) vn = ii;
     float4 qn = S.pos4[vn & ~ANG_BIT];
