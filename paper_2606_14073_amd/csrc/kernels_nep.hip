@@ -1806,7 +1806,9 @@ __global__ void __launch_bounds__(64) k_assemble_angular(Sys S, const real *__re
             for (int n = 0; n < NA; n++) w += P[n * NLM + m] * gS[n];
             a += w * Y[m];
         }
-        W.csa[(size_t)s * lf + i0 + at] = a;   // angular slots of spin carriers lead: s < MAXFE
+        // angular slots of spin carriers lead, so s < MAXFE, but for a row that
+        // overflowed in this step, which is void only at its end
+        if (s < MAXFE) W.csa[(size_t)s * lf + i0 + at] = a;
     }
 }
 
@@ -1869,7 +1871,8 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
             }
             if (r2 < rca2) {
                 const int a = S.xS[(size_t)s * lf + i];
-                J += W.csa[(size_t)(a & 0xff) * lf + i] + W.csa[(size_t)(a >> 8) * lf + j];
+                const int own = min(a & 0xff, MAXFE - 1), rev = min(a >> 8, MAXFE - 1);   // as written, see there
+                J += W.csa[(size_t)own * lf + i] + W.csa[(size_t)rev * lf + j];
             }
             const real g = dotk(CS, f);
             Axx += g * rh[0] * rh[0];
