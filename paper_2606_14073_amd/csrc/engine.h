@@ -31,6 +31,7 @@ constexpr int RCOEF = 4 * NB; // per-atom contracted radial-set coefficients
 constexpr int MCOEF = 3 * NB; // per-spin-carrier contracted magnetic pair coefficients
 
 constexpr int NO_SLOT = 255;  // r2a of a listed neighbour beyond rc_A + skin
+constexpr int NO_RECORD = 0xFFFF;   // xS of a spin pair beyond rc_A, or without room for its spin-angular part
 constexpr int ANG_BIT = (int)0x80000000;   // on a row's entries within rc_A + skin
 
 // flags[] words

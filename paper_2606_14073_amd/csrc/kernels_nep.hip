@@ -214,7 +214,7 @@ __global__ void __launch_bounds__(256) k_active(Sys S, int n) {
             const uint16_t sr = (uint16_t)(pa | prev << 8);
             if (po >= ACT_A) S.actS[(size_t)i * MAXA + po] = sr;
             else if (po >= 0) sS[at * ACT_A + po] = sr;
-            if (px >= 0) sX[px] = po >= 0 ? sr : 0;
+            if (px >= 0) sX[px] = po >= 0 && pa < MAXFE && prev < MAXFE ? sr : NO_RECORD;
         };
         for (int s0 = 0; s0 < len; s0 += 8) {
             const int s = s0 + lane, v = vn, j = v & ~ANG_BIT;
@@ -1828,7 +1828,7 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
     if (i < 0) return;
     const Img R = img_of(S.rep[S.rid[i]]);
     const d4 pi = S.pos[i];
-    const real rc = (real)RC_R, rc2 = rc * rc, rca = (real)RC_A, rca2 = rca * rca;   // as the angular pass
+    const real rc = (real)RC_R, near2 = (real)((RC_A + 0.01) * (RC_A + 0.01));
     const int cnt = S.cntR[i], nfe_all = S.cntFeR[i], nfe = min(nfe_all, MAXFE);
     const size_t ld = S.N, lf = S.N_fe;
     const int *row = S.actR + i;
@@ -1869,10 +1869,11 @@ __global__ void __launch_bounds__(256) k_assemble_pairs(Sys S, const real *__res
                 D += (Ci[NB + k] + mj[NB + k]) * f[k];
                 K += (Ci[2 * NB + k] + mj[2 * NB + k]) * f[k];
             }
-            if (r2 < rca2) {
+            // whether a pair is inside rc_A was decided once, for its list entry;
+            // the distance only saves the farther ones the look
+            if (r2 < near2) {
                 const int a = S.xS[(size_t)s * lf + i];
-                const int own = min(a & 0xff, MAXFE - 1), rev = min(a >> 8, MAXFE - 1);   // as written, see there
-                J += W.csa[(size_t)own * lf + i] + W.csa[(size_t)rev * lf + j];
+                if (a != NO_RECORD) J += W.csa[(size_t)(a & 0xff) * lf + i] + W.csa[(size_t)(a >> 8) * lf + j];
             }
             const real g = dotk(CS, f);
             Axx += g * rh[0] * rh[0];
