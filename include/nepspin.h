@@ -352,8 +352,9 @@ int sl_destroy(sl_sim *s);
  *  10 spin-pair coupling assembly
  *  11 backward (angular set), species 1
  * The read-out also forms the radial-set coefficients that groups 3 and 10 read.
- * Systems of at most 65,536 atoms run groups 0 and 3 in the launches of groups 1
- * and 4, and group 11 in that of group 4.
+ * Systems of at most 65,536 atoms run group 0 in the launches of group 1, and
+ * groups 3 and 11 in that of group 4, unless one of these groups is timed: then
+ * each runs in launches of its own, with the same results.
  * mask: bit g enables group g (0 disables timing). */
 #define SL_NPROF 12
 int sl_profile_enable(sl_sim *s, unsigned mask);

@@ -263,6 +263,7 @@ struct Engine {
     int lds_spins = 0;          // spins of the largest replica where each one's sweep runs in a workgroup, else 0
 
     // kernel-group timing (sl_profile_enable)
+    static constexpr unsigned PROF_SHARED = 1u << 0 | 1u << 1 | 1u << 3 | 1u << 4 | 1u << 11;   // groups that share launches
     unsigned prof_mask = 0;
     std::vector<hipEvent_t> prof_pool;
     std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> prof_open;
@@ -366,6 +367,7 @@ struct Engine {
         S.mag = M && M->structural ? 0 : 1;
         S.wide = S.narrow = 0;
         for (const Replica *r : reps) (r->dev.wide ? S.wide : S.narrow) = 1;
+        S.apart = (prof_mask & PROF_SHARED) != 0;
         S.n_rep = (int)reps.size();
         S.n_cells = n_cells;
         S.rid = rid;

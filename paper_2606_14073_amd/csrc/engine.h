@@ -43,6 +43,7 @@ enum { F_REBUILD = 0, F_OVERFLOW = 1, F_COLOUR = 2, F_NONFINITE = 3, NFLAGS = 8 
 struct Sys {
     int N, N_fe, n_rep, n_cells;
     int wide, narrow;      // some resident replica is wide; some is not
+    int apart;             // 1: kernel groups that wide replicas run in one launch are timed, and launched one by one
     int mag;               // 1: spin-aware model; 0: structural-only (no spin work, N_fe = species-0 count)
     const int *rid;        // [N]
     const int *orig;       // [N] index in the replica's caller order
@@ -120,7 +121,7 @@ enum { PASS_FULL = 0, PASS_SPIN = 1, PASS_SPIN_REUSE = 2 };
 template <typename real>
 void launch_active(const Sys &S, int mode, hipStream_t st);
 // radial set of the replicas with a lane per atom; the angular set of all
-// replicas together with the radial set of the wide ones
+// replicas together with the radial set of the wide ones (unless apart)
 template <typename real>
 void launch_desc_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &W, const d4 *spin, int mode,
                         hipStream_t st);
@@ -132,7 +133,8 @@ void launch_mlp(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int 
 template <typename real>
 void launch_bwd_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &W, hipStream_t st);
 // the angular set of species 0 (spin carriers) or 1; where some replica is
-// wide, species 0 stands for both and for the wide replicas' radial set
+// wide, species 0 stands for both and for the wide replicas' radial set (unless
+// apart)
 template <typename real>
 void launch_bwd_angular(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int species, hipStream_t st);
 template <typename real>

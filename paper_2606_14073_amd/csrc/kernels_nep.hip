@@ -567,11 +567,11 @@ __device__ inline real dotc(const real *c, const real f[NB]) {
 // takes A from it and only recomputes B and q^sa.
 template <typename real>
 __device__ __forceinline__ void desc_angular(const Sys &S, const real *__restrict__ C, const Work<real> &W,
-                                             const d4 *spin, int nbFe, int mode) {
+                                             const d4 *spin, int block, int nbFe, int mode) {
     __shared__ real tile[ANG_ATOMS * ANG_TS];
     const int lane = threadIdx.x & 7, slot = threadIdx.x >> 3;
     bool fe;
-    const int i0 = atom_of_block(S, blockIdx.x, ANG_ATOMS, nbFe, slot, fe), ii = max(i0, 0);
+    const int i0 = atom_of_block(S, block, ANG_ATOMS, nbFe, slot, fe), ii = max(i0, 0);
     const bool reuse = mode == PASS_SPIN_REUSE, mag = S.mag && fe;
     const int *row = S.actA + (size_t)ii * MAXA;
     const d4 pi = S.pos[ii];
@@ -742,17 +742,18 @@ __device__ __forceinline__ void desc_angular(const Sys &S, const real *__restric
 template <typename real>
 __global__ void __launch_bounds__(64) k_desc_angular(Sys S, const real *__restrict__ C, Work<real> W,
                                                      const d4 *spin, int nbFe, int mode) {
-    desc_angular(S, C, W, spin, nbFe, mode);
+    desc_angular(S, C, W, spin, blockIdx.x, nbFe, mode);
 }
 
 // the same and the radial set of the wide replicas, in blocks of the same eight
 // atoms: the two do not depend on each other, and a small system is bound by
-// the length of its chain of launches
+// the length of its chain of launches. Blocks from b0 on.
 template <typename real>
 __global__ void __launch_bounds__(64, 2) k_desc_both(Sys S, const real *__restrict__ C, Work<real> W, const d4 *spin,
-                                                  int nbFe, int nb, int mode) {
-    if ((int)blockIdx.x < nb) desc_angular(S, C, W, spin, nbFe, mode);
-    else desc_radial<real, WIDE_LANES, 64>(S, C, W, spin, blockIdx.x - nb, nbFe);
+                                                  int b0, int nbFe, int nb, int mode) {
+    const int b = b0 + blockIdx.x;
+    if (b < nb) desc_angular(S, C, W, spin, b, nbFe, mode);
+    else desc_radial<real, WIDE_LANES, 64>(S, C, W, spin, b - nb, nbFe);
 }
 
 // -------------------------------------------------------------------------
@@ -1655,12 +1656,14 @@ __global__ void __launch_bounds__(64) k_bwd_angular(Sys S, const real *__restric
 
 // The whole backward pass of a batch with wide replicas: the angular set of
 // both species and, of the wide replicas, the radial set and the magnetic pairs,
-// which do not depend on each other, in blocks of eight atoms (see k_desc_both).
+// which do not depend on each other, in blocks of eight atoms (see k_desc_both),
+// from b0 on.
 template <typename real, bool MAG>
-__global__ void __launch_bounds__(64, 2) k_bwd_both(Sys S, const real *__restrict__ C, Work<real> W, int nbFe, int nb) {
+__global__ void __launch_bounds__(64, 2) k_bwd_both(Sys S, const real *__restrict__ C, Work<real> W, int b0, int nbFe,
+                                                    int nb) {
     __shared__ real sQ[ANG_ATOMS * qstride<MAG>()];
     __shared__ double sAt[ANG_ATOMS * AT_W];
-    int b = blockIdx.x;
+    int b = b0 + blockIdx.x;
     if (b < nbFe) return bwd_angular<real, MAG>(S, C, W, 0, S.N_fe, b, sQ, sAt);
     if (b < nb) return bwd_angular<real, false>(S, C, W, S.N_fe, S.N, b - nbFe, sQ, sAt);
     b -= nb;
@@ -1953,15 +1956,41 @@ void launch_active(const Sys &S, int mode, hipStream_t st) {
     if (n) hipLaunchKernelGGL(k_active<real>, dim3(nblk(n, 32)), dim3(256), 0, st, S, n);
 }
 
+// The launches that wide replicas share cover blocks [b, e) of theirs: all of
+// them, or where their groups are timed (S.apart) each group's own. The kernel is
+// the same, and so are the bits.
+template <typename real>
+void desc_both(const Sys &S, const ModelDev<real> &M, const Work<real> &W, const d4 *spin, int b, int e, int nb_fe,
+               int nb, int mode, hipStream_t st) {
+    if (e > b)
+        hipLaunchKernelGGL(k_desc_both<real>, dim3(e - b), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, spin, b, nb_fe, nb,
+                           mode);
+}
+template <typename real>
+void bwd_both(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int b, int e, int nb_fe, int nb,
+              hipStream_t st) {
+    if (e <= b) return;
+    const dim3 g(e - b), t(8 * ANG_ATOMS);
+    if (S.mag) hipLaunchKernelGGL((k_bwd_both<real, true>), g, t, 0, st, S, M.cR, W, b, nb_fe, nb);
+    else hipLaunchKernelGGL((k_bwd_both<real, false>), g, t, 0, st, S, M.cR, W, b, nb_fe, nb);
+}
+
 // spin-step passes (PASS_SPIN, PASS_SPIN_REUSE) cover the spin carriers only:
 // the frozen-Fp magnetic energy has no term on atoms without a spin
 template <typename real>
 void launch_desc_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &W, const d4 *spin, int mode,
                         hipStream_t st) {
-    if (S.N == 0 || !S.narrow) return;
-    NEP_SPLIT(256)
-    const int nb = mode == PASS_FULL ? nb_fe + nb_ge : nb_fe;
-    if (nb) hipLaunchKernelGGL(k_desc_radial<real>, dim3(nb), dim3(256), 0, st, S, M.cR, W, spin, nb_fe);
+    if (S.N == 0) return;
+    if (S.narrow) {
+        NEP_SPLIT(256)
+        const int nb = mode == PASS_FULL ? nb_fe + nb_ge : nb_fe;
+        if (nb) hipLaunchKernelGGL(k_desc_radial<real>, dim3(nb), dim3(256), 0, st, S, M.cR, W, spin, nb_fe);
+    }
+    if (S.wide && S.apart) {
+        NEP_SPLIT(ANG_ATOMS)
+        const int nb = mode == PASS_FULL ? nb_fe + nb_ge : nb_fe;
+        desc_both(S, M, W, spin, nb, 2 * nb, nb_fe, nb, mode, st);
+    }
 }
 
 template <typename real>
@@ -1970,10 +1999,8 @@ void launch_desc_angular(const Sys &S, const ModelDev<real> &M, const Work<real>
     if (S.N == 0) return;
     NEP_SPLIT(ANG_ATOMS)
     const int nb = mode == PASS_FULL ? nb_fe + nb_ge : nb_fe;
-    if (!nb) return;
-    if (S.wide)
-        hipLaunchKernelGGL(k_desc_both<real>, dim3(2 * nb), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, spin, nb_fe, nb, mode);
-    else
+    if (S.wide) desc_both(S, M, W, spin, 0, S.apart ? nb : 2 * nb, nb_fe, nb, mode, st);
+    else if (nb)
         hipLaunchKernelGGL(k_desc_angular<real>, dim3(nb), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, spin, nb_fe, mode);
 }
 
@@ -2001,10 +2028,16 @@ void launch_mlp(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int 
 template <typename real>
 void launch_bwd_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &W, hipStream_t st) {
     if (S.N == 0) return;
-    NEP_SPLIT(256)
-    if (!S.narrow) return;
-    hipLaunchKernelGGL(k_bwd_radial<real>, dim3(nb_fe + nb_ge), dim3(256), 0, st, S, M.cR, W, nb_fe);
-    if (nb_fe && S.mag) hipLaunchKernelGGL(k_bwd_mag<real>, dim3(nb_fe), dim3(256), 0, st, S, W);
+    if (S.narrow) {
+        NEP_SPLIT(256)
+        hipLaunchKernelGGL(k_bwd_radial<real>, dim3(nb_fe + nb_ge), dim3(256), 0, st, S, M.cR, W, nb_fe);
+        if (nb_fe && S.mag) hipLaunchKernelGGL(k_bwd_mag<real>, dim3(nb_fe), dim3(256), 0, st, S, W);
+    }
+    if (S.wide && S.apart) {
+        NEP_SPLIT(ANG_ATOMS)
+        const int nb = nb_fe + nb_ge;
+        bwd_both(S, M, W, nb, 2 * nb + (S.mag ? nb_fe : 0), nb_fe, nb, st);
+    }
 }
 
 template <typename real>
@@ -2012,14 +2045,9 @@ void launch_bwd_angular(const Sys &S, const ModelDev<real> &M, const Work<real> 
     if (S.N == 0) return;
     NEP_SPLIT(ANG_ATOMS)
     if (S.wide) {
-        if (species) return;
         const int nb = nb_fe + nb_ge;
-        if (S.mag)
-            hipLaunchKernelGGL((k_bwd_both<real, true>), dim3(2 * nb + nb_fe), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W,
-                               nb_fe, nb);
-        else
-            hipLaunchKernelGGL((k_bwd_both<real, false>), dim3(2 * nb), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, nb_fe,
-                               nb);
+        if (S.apart) bwd_both(S, M, W, species ? nb_fe : 0, species ? nb : nb_fe, nb_fe, nb, st);
+        else if (species == 0) bwd_both(S, M, W, 0, 2 * nb + (S.mag ? nb_fe : 0), nb_fe, nb, st);
         return;
     }
     if (species == 0 && nb_fe) {
