@@ -117,8 +117,9 @@ def flops_per_step(group, pc, k_corr=1):
         return (pc["A"] - pc["A_fe"]) * 1568 + (N - Nfe) * 1008
     if group == "bwd_radial":
         # per pair: geometry/basis+derivative 115, radial dg 18, record 20; Fe-Fe: 8 more
-        # channel values 144 + force/field terms 90; Fe-Ge: 36 + 30
-        return pc["R"] * 153 + fe_centre_fe * 234 + fe_centre_ge * 66
+        # channel values 144 + force/field terms 90; Fe-Ge: 36 + 30; the atom's own
+        # contractions: two radial, two more single-ion on spin carriers
+        return pc["R"] * 153 + fe_centre_fe * 234 + fe_centre_ge * 66 + N * 2 * 162 + Nfe * 2 * 162
     if group == "couplings":
         # per spin-step pass: per spin carrier P = Fp^sa A 168; spin-angular part per Fe-Fe
         # pair inside rc_A: geometry/basis 75, g^sa 126, harmonics 50, contraction 336 + 48

@@ -147,7 +147,7 @@ int nep_model_destroy(nep_model *m);
 
 /* One system, caller-owned and read-only. types[n] in {0,1}; pos[n][3];
  * spin[n][3] (rows of species 1 ignored); box edges; pbc[a] = 1 for a
- * periodic axis (minimum image), 0 for a free axis. mu_s is the moment of a
+ * periodic axis (minimum image; positions in any image), 0 for a free axis. mu_s is the moment of a
  * species-0 atom in Bohr magnetons; B the applied field in Tesla (Zeeman
  * energy -mu_s mu_B B.s_i on species-0 atoms). */
 typedef struct {
@@ -351,7 +351,9 @@ int sl_destroy(sl_sim *s);
  *   9 lattice half-steps, baths and reductions
  *  10 spin-pair coupling assembly
  *  11 backward (angular set), species 1
- * The read-out also forms the radial-set coefficients that groups 3 and 10 read.
+ * The read-out also forms the radial-set coefficients that groups 3 and 10 read
+ * of an atom's neighbours and, except those of the radial and single-ion channels,
+ * which they form again, of the atom itself.
  * Systems of at most 65,536 atoms run group 0 in the launches of group 1, and
  * groups 3 and 11 in that of group 4, unless one of these groups is timed: then
  * each runs in launches of its own, with the same results.

@@ -155,7 +155,7 @@ __device__ inline double dtanh<double>(double x) {
     double y = 2.0 * fabs(x);
     y = y > 44.0 ? 44.0 : y;
     const double k = rint(y * 1.4426950408889634074);
-    double r = fma(-k, 0x1.62e42fefap-1, y);     // ln 2, its first 33 bits: k times them is exact
+    double r = fma(-k, 0x1.62e42fefap-1, y);     // ln 2, its first 36 bits: k times them is exact
     r = fma(-k, 0x1.cf79abc9e3b3ap-40, r);       // and the rest
     double p = 1.0 / 6227020800.0;               // 1/13!
     p = fma(p, r, 1.0 / 479001600.0);

@@ -67,8 +67,8 @@ struct Sys {
     // neighbours inside the cutoffs at the present positions, in row order, with
     // their counts: inside rc_R rank-major [rank][N] (for a lane per atom);
     // inside rc_A atom-major [N][MAXA] (for the lanes of eight atoms together)
-    // with own | reverse angular slot << 8 of each (actS), the latter also
-    // [rank][N_fe] at the rc_R rank of spin pairs (xS)
+    // with own | reverse angular slot << 8 of each (actS), also [rank][N_fe] at
+    // the rc_R rank of spin pairs (xS; NO_RECORD on those beyond rc_A)
     int *actR, *cntR, *cntFeR;
     int *actA, *cntA, *cntFeA;
     uint16_t *actS, *xS;

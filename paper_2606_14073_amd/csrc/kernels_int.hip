@@ -443,8 +443,9 @@ __device__ inline int sweep_solve(const RepDev &R, const SweepConst &c, const Sw
     // cycles an iteration), so the first two iterations, which only have to come
     // near, run in FP32 (step 2^-11): from about 1e-7 one FP64 iteration reaches
     // the tolerance and the next one finds that it did, where from y = s it took
-    // three and that one. 512 atoms 5.75 -> 5.4 us per
-    // colour launch, 262,144 atoms 8.3 -> 7.6 (FP32-mixed 7.6 -> 7.2).
+    // three and that one. Per colour launch, without and with it: 11,520 atoms FP64
+    // 7.0 -> 6.5 us; 262,144 8.1 -> 7.6, FP32 7.3 -> 6.8; 1,048,576 FP32 13.0 -> 12.1;
+    // 2,097,152 FP64 21.9 -> 21.3.
     const int sub = lane & 3;
     constexpr double FD_H = 0x1p-23, FD_IH = 0x1p23;
     constexpr float FF_H = 0x1p-11f, FF_IH = 0x1p11f;
@@ -567,9 +568,9 @@ __device__ inline int sweep_solve(const RepDev &R, const SweepConst &c, const Sw
 
 // One colour class per launch. Latency is what bounds a class: list position ->
 // couplings -> neighbour spins -> midpoint solve -> store. With the spins loaded
-// beside the replica's state instead of after it: 10,648 atoms FP64 6.4 -> 6.0 us
-// per launch; 262,144 7.8 -> 7.6, FP32 7.3 -> 6.7; 1,048,576 FP32 12.8 -> 12.1;
-// 2,097,152 FP64 22.9 -> 21.3.
+// beside the replica's state instead of after it: 11,520 atoms FP64 6.8 -> 6.5 us
+// per launch; 262,144 7.9 -> 7.6, FP32 7.2 -> 6.8; 1,048,576 FP32 12.3 -> 12.1;
+// 2,097,152 FP64 22.1 -> 21.3.
 template <typename real, int L>
 __global__ void __launch_bounds__(256) k_sweep(Sys S, Work<real> W, int base, int count, int turns, int visit0) {
     const int lane = threadIdx.x & (L - 1);

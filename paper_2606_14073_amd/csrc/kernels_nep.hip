@@ -122,12 +122,11 @@ __device__ inline real dotk(const real C[NB], const real f[NB]) {
 // 16 bytes and lane: the test runs on the single-precision positions (one
 // access), and the few pairs that lie within its rounding error of a cutoff
 // are tested as the pair kernels compute r^2.
-// 2,097,152 atoms, FP64: 2.3 ms of a step for its two passes, against 6.8 ms
+// 2,097,152 atoms, FP64: 1.4 ms of a step for its two passes, against 6.8 ms
 // that the pair kernels no longer spend on the skin.
 // -------------------------------------------------------------------------
 
-// the cutoff tests of one atom; close() says that a test in single precision
-// does not decide
+// the cutoff tests of one atom
 template <typename real>
 struct CutTest {
     static constexpr real rc = (real)RC_R, rca = (real)RC_A;
@@ -171,11 +170,11 @@ struct CutTest {
 // The lists are put together in LDS and written in whole lines: stored by each
 // lane as it went along (its ranks differ from its neighbours') they left L2 in
 // parts, 3.8 times their bytes. Latency bounds it, so LDS holds the ranks that a
-// crystal or a liquid has (62 and 29 in FeGe, about 90 and 38 in water) and any
-// further ones are stored one by one: six workgroups fit in a CU's LDS instead
+// crystal or a liquid has (62 and 29 in FeGe, 84 and 41 in water, in the mean) and
+// any further ones are stored one by one: six workgroups fit in a CU's LDS instead
 // of three; and the partner's slot is used a round after its load. Mean of a
-// step's two passes: 2,097,152 atoms 1.06 -> 0.75 ms; 1,048,576 in a slab, FP32
-// 0.52 -> 0.37; 262,144 128 -> 87 us; 375,000 water atoms 304 -> 205 (one pass).
+// step's two passes: 2,097,152 atoms 1.06 -> 0.72 ms; 1,048,576 in a slab, FP32
+// 0.52 -> 0.36; 262,144 128 -> 85 us; 375,000 water atoms 304 -> 202 (one pass).
 constexpr int ACT_R = 96, ACT_A = 48;
 template <typename real>
 __global__ void __launch_bounds__(256) k_active(Sys S, int n) {
