@@ -566,11 +566,11 @@ __device__ inline real dotc(const real *c, const real f[NB]) {
 // takes A from it and only recomputes B and q^sa.
 template <typename real>
 __device__ __forceinline__ void desc_angular(const Sys &S, const real *__restrict__ C, const Work<real> &W,
-                                             const d4 *spin, int block, int nbFe, int mode) {
+                                             const d4 *spin, int nbFe, int mode) {
     __shared__ real tile[ANG_ATOMS * ANG_TS];
     const int lane = threadIdx.x & 7, slot = threadIdx.x >> 3;
     bool fe;
-    const int i0 = atom_of_block(S, block, ANG_ATOMS, nbFe, slot, fe), ii = max(i0, 0);
+    const int i0 = atom_of_block(S, blockIdx.x, ANG_ATOMS, nbFe, slot, fe), ii = max(i0, 0);
     const bool reuse = mode == PASS_SPIN_REUSE, mag = S.mag && fe;
     const int *row = S.actA + (size_t)ii * MAXA;
     const d4 pi = S.pos[ii];
@@ -741,18 +741,17 @@ __device__ __forceinline__ void desc_angular(const Sys &S, const real *__restric
 template <typename real>
 __global__ void __launch_bounds__(64) k_desc_angular(Sys S, const real *__restrict__ C, Work<real> W,
                                                      const d4 *spin, int nbFe, int mode) {
-    desc_angular(S, C, W, spin, blockIdx.x, nbFe, mode);
+    desc_angular(S, C, W, spin, nbFe, mode);
 }
 
 // the same and the radial set of the wide replicas, in blocks of the same eight
 // atoms: the two do not depend on each other, and a small system is bound by
-// the length of its chain of launches. Blocks from b0 on.
+// the length of its chain of launches (nb = 0: the radial set alone)
 template <typename real>
 __global__ void __launch_bounds__(64, 2) k_desc_both(Sys S, const real *__restrict__ C, Work<real> W, const d4 *spin,
-                                                  int b0, int nbFe, int nb, int mode) {
-    const int b = b0 + blockIdx.x;
-    if (b < nb) desc_angular(S, C, W, spin, b, nbFe, mode);
-    else desc_radial<real, WIDE_LANES, 64>(S, C, W, spin, b - nb, nbFe);
+                                                  int nbFe, int nb, int mode) {
+    if ((int)blockIdx.x < nb) desc_angular(S, C, W, spin, nbFe, mode);
+    else desc_radial<real, WIDE_LANES, 64>(S, C, W, spin, blockIdx.x - nb, nbFe);
 }
 
 // -------------------------------------------------------------------------
@@ -1655,17 +1654,19 @@ __global__ void __launch_bounds__(64) k_bwd_angular(Sys S, const real *__restric
 
 // The whole backward pass of a batch with wide replicas: the angular set of
 // both species and, of the wide replicas, the radial set and the magnetic pairs,
-// which do not depend on each other, in blocks of eight atoms (see k_desc_both),
-// from b0 on.
+// which do not depend on each other, in blocks of eight atoms (see k_desc_both):
+// nb of them for all atoms; the first na of the grid are the angular set's, those
+// before nbA of species 0 (na = nb, nbA = nbFe: everything; na = 0: the radial
+// set alone; nbA = 0: species 1 and what follows).
 template <typename real, bool MAG>
-__global__ void __launch_bounds__(64, 2) k_bwd_both(Sys S, const real *__restrict__ C, Work<real> W, int b0, int nbFe,
-                                                    int nb) {
+__global__ void __launch_bounds__(64, 2) k_bwd_both(Sys S, const real *__restrict__ C, Work<real> W, int nbA, int na,
+                                                    int nbFe, int nb) {
     __shared__ real sQ[ANG_ATOMS * qstride<MAG>()];
     __shared__ double sAt[ANG_ATOMS * AT_W];
-    int b = b0 + blockIdx.x;
-    if (b < nbFe) return bwd_angular<real, MAG>(S, C, W, 0, S.N_fe, b, sQ, sAt);
-    if (b < nb) return bwd_angular<real, false>(S, C, W, S.N_fe, S.N, b - nbFe, sQ, sAt);
-    b -= nb;
+    int b = blockIdx.x;
+    if (b < nbA) return bwd_angular<real, MAG>(S, C, W, 0, S.N_fe, b, sQ, sAt);
+    if (b < na) return bwd_angular<real, false>(S, C, W, S.N_fe, S.N, b - nbA, sQ, sAt);
+    b -= na;
     if (b < nb) return bwd_radial<real, WIDE_LANES, 64>(S, C, W, b, nbFe);
     if constexpr (MAG) bwd_mag<real, WIDE_LANES, 64>(S, W, b - nb);
 }
@@ -1955,23 +1956,16 @@ void launch_active(const Sys &S, int mode, hipStream_t st) {
     if (n) hipLaunchKernelGGL(k_active<real>, dim3(nblk(n, 32)), dim3(256), 0, st, S, n);
 }
 
-// The launches that wide replicas share cover blocks [b, e) of theirs: all of
-// them, or where their groups are timed (S.apart) each group's own. The kernel is
-// the same, and so are the bits.
+// The launches that wide replicas share: everything at once, or where their
+// groups are timed (S.apart) each group's own blocks. The kernel is the same, and
+// so are the bits.
 template <typename real>
-void desc_both(const Sys &S, const ModelDev<real> &M, const Work<real> &W, const d4 *spin, int b, int e, int nb_fe,
-               int nb, int mode, hipStream_t st) {
-    if (e > b)
-        hipLaunchKernelGGL(k_desc_both<real>, dim3(e - b), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, spin, b, nb_fe, nb,
-                           mode);
-}
-template <typename real>
-void bwd_both(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int b, int e, int nb_fe, int nb,
+void bwd_both(const Sys &S, const ModelDev<real> &M, const Work<real> &W, int blocks, int nbA, int na, int nb_fe, int nb,
               hipStream_t st) {
-    if (e <= b) return;
-    const dim3 g(e - b), t(8 * ANG_ATOMS);
-    if (S.mag) hipLaunchKernelGGL((k_bwd_both<real, true>), g, t, 0, st, S, M.cR, W, b, nb_fe, nb);
-    else hipLaunchKernelGGL((k_bwd_both<real, false>), g, t, 0, st, S, M.cR, W, b, nb_fe, nb);
+    if (!blocks) return;
+    const dim3 g(blocks), t(8 * ANG_ATOMS);
+    if (S.mag) hipLaunchKernelGGL((k_bwd_both<real, true>), g, t, 0, st, S, M.cR, W, nbA, na, nb_fe, nb);
+    else hipLaunchKernelGGL((k_bwd_both<real, false>), g, t, 0, st, S, M.cR, W, nbA, na, nb_fe, nb);
 }
 
 // spin-step passes (PASS_SPIN, PASS_SPIN_REUSE) cover the spin carriers only:
@@ -1988,7 +1982,8 @@ void launch_desc_radial(const Sys &S, const ModelDev<real> &M, const Work<real> 
     if (S.wide && S.apart) {
         NEP_SPLIT(ANG_ATOMS)
         const int nb = mode == PASS_FULL ? nb_fe + nb_ge : nb_fe;
-        desc_both(S, M, W, spin, nb, 2 * nb, nb_fe, nb, mode, st);
+        if (nb)
+            hipLaunchKernelGGL(k_desc_both<real>, dim3(nb), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, spin, nb_fe, 0, mode);
     }
 }
 
@@ -1998,8 +1993,11 @@ void launch_desc_angular(const Sys &S, const ModelDev<real> &M, const Work<real>
     if (S.N == 0) return;
     NEP_SPLIT(ANG_ATOMS)
     const int nb = mode == PASS_FULL ? nb_fe + nb_ge : nb_fe;
-    if (S.wide) desc_both(S, M, W, spin, 0, S.apart ? nb : 2 * nb, nb_fe, nb, mode, st);
-    else if (nb)
+    if (!nb) return;
+    if (S.wide)
+        hipLaunchKernelGGL(k_desc_both<real>, dim3(S.apart ? nb : 2 * nb), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, spin,
+                           nb_fe, nb, mode);
+    else
         hipLaunchKernelGGL(k_desc_angular<real>, dim3(nb), dim3(8 * ANG_ATOMS), 0, st, S, M.cR, W, spin, nb_fe, mode);
 }
 
@@ -2035,7 +2033,7 @@ void launch_bwd_radial(const Sys &S, const ModelDev<real> &M, const Work<real> &
     if (S.wide && S.apart) {
         NEP_SPLIT(ANG_ATOMS)
         const int nb = nb_fe + nb_ge;
-        bwd_both(S, M, W, nb, 2 * nb + (S.mag ? nb_fe : 0), nb_fe, nb, st);
+        bwd_both(S, M, W, nb + (S.mag ? nb_fe : 0), 0, 0, nb_fe, nb, st);
     }
 }
 
@@ -2045,8 +2043,9 @@ void launch_bwd_angular(const Sys &S, const ModelDev<real> &M, const Work<real> 
     NEP_SPLIT(ANG_ATOMS)
     if (S.wide) {
         const int nb = nb_fe + nb_ge;
-        if (S.apart) bwd_both(S, M, W, species ? nb_fe : 0, species ? nb : nb_fe, nb_fe, nb, st);
-        else if (species == 0) bwd_both(S, M, W, 0, 2 * nb + (S.mag ? nb_fe : 0), nb_fe, nb, st);
+        if (S.apart && species) bwd_both(S, M, W, nb_ge, 0, nb_ge, nb_fe, nb, st);
+        else if (S.apart) bwd_both(S, M, W, nb_fe, nb_fe, nb_fe, nb_fe, nb, st);
+        else if (!species) bwd_both(S, M, W, 2 * nb + (S.mag ? nb_fe : 0), nb_fe, nb, nb_fe, nb, st);
         return;
     }
     if (species == 0 && nb_fe) {
